@@ -18,6 +18,7 @@ from __future__ import annotations
 import argparse
 import hashlib
 import json
+import math
 import os
 import sys
 import time
@@ -370,8 +371,11 @@ def run_workload(torch, nwg, name: str, tile: str, precision: str, steps: int, w
     direct_flop = float(sum(L.direct_flop for L in wl.layers))
     # per-stage accounting summed over layers
     stages = {}
-    for p, (ms, cnt) in zip(plans, timing):
+    for p, L, (ms, cnt) in zip(plans, wl.layers, timing):
         bf = stage_bytes_flops(p.info)
+        if p.direct:                         # one kernel: x and the plain weights in, y out
+            bf = {"contraction": (4 * (L.B * L.M * L.H * L.W + math.prod(L.w_shape) +
+                                       L.B * L.N * L.Ho * L.Wo), float(L.direct_flop))}
         parts = p.info["pipeline_parts"]
         for si, sname in enumerate(STAGES):
             if sname == "kernel_transform" or cnt[si] == 0:
@@ -393,7 +397,8 @@ def run_workload(torch, nwg, name: str, tile: str, precision: str, steps: int, w
                                     **({"fused_input": True} if p.info["fused_input"]
                                        and sname == "contraction" else {}),
                                     **({"fused_conv": True} if p.info["fused_conv"]
-                                       and sname == "contraction" else {})})
+                                       and sname == "contraction" else {}),
+                                    **({"direct": True} if p.direct else {})})
     # split precision: the MFMAs run on bf16 and execute 4 partial products
     # per algorithmic multiply-add
     split = any(p.info["precision"] == nwg.NWG_PRECISION_BF16_SPLIT for p in plans)

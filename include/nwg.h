@@ -115,7 +115,8 @@ typedef struct nwg_plan nwg_plan;
  *     1.6x fewer contraction FLOPs per output but 2.4x the transformed
  *     weights, and few 36 x 36 tiles leave its MFMA tiles mostly empty --,
  *     and F(2x2,3x3) otherwise (always for depthwise plans).  info.tile
- *     reports the tile taken. */
+ *     reports the tile taken.  Layers on which no nest pays run direct
+ *     (nwg_plan_direct, nwg_conv2d). */
 /*   NWG_TILE_LD_F2X2_3X3: the linear decomposition of Sec. II.B (Fig. 2),
  *     the method the paper compares nesting with, on the same F(2x2,3x3)
  *     kernels: the r x r kernel is cut into c x c sub-kernels of 3 x 3
@@ -289,6 +290,9 @@ void nwg_plan_destroy(nwg_plan* plan);
 /* Copy the plan's geometry into *out. */
 int nwg_plan_query(const nwg_plan* plan, nwg_plan_info* out);
 
+/* 1 when nwg_conv2d runs the plan's layer direct (see there), else 0. */
+int nwg_plan_direct(const nwg_plan* plan);
+
 /* y = conv(x, w), the correlation of Sec. II.A, by the steps of Sec. III.B:
  * the nested kernel transform (only when w differs from the cached weight
  * pointer or after nwg_plan_set_weights), then the nested input transform,
@@ -300,7 +304,14 @@ int nwg_plan_query(const nwg_plan* plan, nwg_plan_info* out);
  * directly.  The weight cache is keyed by the pointer only: mutating w in
  * place, or passing a new weight tensor at a freed one's address, requires
  * nwg_plan_set_weights before the next call.  NWG_EINVAL for a NULL
- * argument, NWG_EHIP when a launch fails. */
+ * argument, NWG_EHIP when a launch fails.
+ * On an NWG_TILE_AUTO plan in fp32, layers that measured faster so (small maps
+ * or few channels up to r = 15, few channels above, depthwise from r = 8) run
+ * direct: one kernel sums the correlation of Sec. II.A itself, x -> y (timed as
+ * the contraction, index 2), on a plain copy of w that the plan holds in place
+ * of U (its copy is timed as the kernel transform, index 0).  The info and the
+ * stage calls of such a plan are those of its tile; nwg_conv2d on any other
+ * tile always runs that tile's nest. */
 int nwg_conv2d(nwg_plan* plan, const float* x, const float* w, float* y, void* stream);
 
 /* Re-run the kernel transform of w into the plan's cached U now. */
@@ -379,7 +390,8 @@ int nwg_plan_get_timing(nwg_plan* plan, double ms[4], long long count[4]);
  * capture, tight serving loops, harnesses that forbid hipMalloc.
  * nwg_conv2d_noalloc computes what nwg_conv2d computes on a plan created by
  * nwg_plan_create_pad(B, M, N, H, W, r, pad, tile) (dense, fp32, no
- * pipeline), with the same kernels, but takes that plan's workspace (U; V
+ * pipeline), with the same kernels (direct ones included: these need no
+ * workspace here), but takes that plan's workspace (U; V
  * and Z where the plan holds them; each rounded up to 256 bytes) from a
  * static device array of NWG_NOALLOC_SCRATCH_BYTES that the library holds on
  * every GPU it runs on until the process ends, and transforms w on every

@@ -1,0 +1,641 @@
+// Direct correlation (the definition of Sec. II.A) of layers on which the
+// nest does not pay on this machine, x -> y in one kernel with nothing in
+// memory between: NWG_TILE_AUTO plans take it where it measured faster
+// (direct_route in plan.cpp).  Three kernels, fp32 throughout:
+//
+//   direct_toeplitz  depthwise layers, and dense ones with one or two output
+//     channels, with large kernels: a row of taps against a row of the map is
+//     a product with a banded (Toeplitz) matrix, on fp32 MFMA.
+//   direct_valu      depthwise layers with small kernels and dense ones with
+//     few output channels: each lane holds a run of outputs in registers and
+//     takes the weights as scalars.
+//   direct_mfma      other small dense layers: the implicit product of the
+//     weights (output channels x channels and taps) and the map's windows, on
+//     fp32 MFMA.
+//
+// Every kernel adds its products in two steps (short sums, then their total),
+// so that the rounding of a long running sum stays below the nest's own.
+//
+// Operand lane maps of v_mfma_f32_16x16x4f32 (wave64):
+//   A (16x4):  lane l holds A[l%16][l/16]
+//   B (4x16):  lane l holds B[l/16][l%16]
+//   D (16x16): lane l, register v holds D[4*(l/16)+v][l%16]
+#include "direct.h"
+
+#include "nwg_internal.h"
+
+#include <type_traits>
+#include <utility>
+
+namespace nwg {
+namespace {
+
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+
+// Direct global->LDS copy of BYTES bytes per lane (asynchronous; a barrier's
+// wait covers it), the lanes side by side at dst.  Offsets past the resource's
+// range load 0.
+constexpr unsigned kOutside = 0x80000000u;
+
+template <int BYTES = 4>
+__device__ __forceinline__ void copy_lds(__amdgpu_buffer_rsrc_t r, float* dst, unsigned off) {
+  auto* d = (__attribute__((address_space(3))) void*)dst;
+  if constexpr (BYTES == 16)
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, d, 16, (int)off, 0, 0, 0);
+  else
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, d, 4, (int)off, 0, 0, 0);
+}
+
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t read_rsrc(const float* base, unsigned bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(base), 0, (int)bytes, 0x00020000);
+}
+
+// Waits for this wave's copies, then for the work-group's: a barrier alone does
+// not wait for copies that another wave will read.
+__device__ __forceinline__ void copies_done() {
+  wait_vmcnt<0>();
+  __syncthreads();
+}
+
+// Copies nch planes' boxes to LDS: BH rows from r0 and BW columns from c0 of
+// planes xb + m * plane, zero outside the image and for m >= mvalid; box
+// (m, row, col) at dst[(m * BHC + row) * BW + col], BHC >= BH rows a box.  VEC
+// values at a time (4: W, BW and c0 are multiples of 4 and xb is 16-byte
+// aligned).  The lanes walk the flat boxes in batches of FB independent loads
+// through a resource that spans the planes (less than 2^31 bytes): the hardware
+// supplies the zeros.  Direct global->LDS copies of a dword per lane took longer
+// (a 9x9 32 -> 1 layer 47 us against 38).
+template <int VEC>
+__device__ __forceinline__ void stage_box(const float* __restrict__ xb, size_t plane_, int mvalid,
+                                          float* dst, int nch, int BH, int BHC, int BW, int H,
+                                          int W, int r0, int c0) {
+  constexpr int FB = 8;
+  const int tid = threadIdx.x, NT = blockDim.x, plane = (int)plane_;
+  const int BU = BW / VEC, CS = BHC * BU, nel = nch * CS;
+  const __amdgpu_buffer_rsrc_t rs = read_rsrc(xb, 4u * (unsigned)(mvalid * plane));
+  // (channel, row, column) of this lane's values and their offset in the planes
+  int m = tid / CS;
+  int row = (tid - m * CS) / BU;
+  int col = tid - m * CS - row * BU;
+  int off = m * plane + (r0 + row) * W + c0 + VEC * col;
+  const int dm = NT / CS, drow = (NT - dm * CS) / BU, dcol = NT - dm * CS - drow * BU;
+  const int doff = dm * plane + drow * W + VEC * dcol, dwrap = plane - BHC * W;
+  for (int e0 = tid; e0 < nel; e0 += NT * FB) {
+    float v[FB][VEC];
+#pragma unroll
+    for (int k = 0; k < FB; ++k) {
+      const bool ok = (unsigned)(r0 + row) < (unsigned)H &&
+                      (unsigned)(c0 + VEC * col) < (unsigned)W && row < BH && m < mvalid;
+      const int o = ok ? 4 * off : (int)kOutside;
+      if constexpr (VEC == 4) {
+        typedef unsigned u4 __attribute__((ext_vector_type(4)));
+        const u4 q = __builtin_amdgcn_raw_buffer_load_b128(rs, o, 0, 0);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) v[k][j] = __uint_as_float(q[j]);
+      } else {
+        v[k][0] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, o, 0, 0));
+      }
+      m += dm;
+      row += drow;
+      col += dcol;
+      off += doff;
+      if (col >= BU) {
+        col -= BU;
+        ++row;
+        off += W - BW;
+      }
+      if (row >= BHC) {
+        row -= BHC;
+        ++m;
+        off += dwrap;
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < FB; ++k) {
+      const int e = e0 + k * NT;
+      if (e < nel) {
+        if constexpr (VEC == 4)
+          *reinterpret_cast<float4*>(dst + 4 * e) = make_float4(v[k][0], v[k][1], v[k][2], v[k][3]);
+        else
+          dst[e] = v[k][0];
+      }
+    }
+  }
+}
+
+// ---- depthwise / few output channels, large kernels -------------------------
+// One output channel (blockIdx.y) and a box of 16 WR x 16 WC outputs of one
+// image per work-group; wave (wr, wc) owns a tile of 16 x 16.  Per tap row u,
+// the tile's 16 rows of x (A: 16 rows x 4 columns per step) meet the banded
+// matrix of the tap row (B[k][j] = w[u][4 s + k - j]), in S steps of 4 columns
+// covering the 16 + r - 1 columns a tile reads.  Steps whose columns (and tap
+// rows whose rows) lie wholly outside the image are left out.  One tile a wave
+// and 3 to 5 work-groups a CU: two or four tiles a wave (a fragment of the band
+// or of the rows shared) took 1.4 to 2 times as long, as fewer waves hid the LDS
+// reads.  31x31 depthwise, 16 x 128 x 56 x 56: 183 us, 67 TFLOP/s of the
+// direct sum (the fused nest and its output transform: 1905 us).
+template <int S, int VEC>
+__global__ __launch_bounds__(256) void direct_toeplitz(
+    const float* __restrict__ x, const float* __restrict__ w, float* __restrict__ y, int M, int N,
+    int dw, int r, int H, int W, int pad, int Ho, int Wo, int WR, int WC, int nbx, int nby,
+    int BW) {
+  constexpr int WS = 4 * S + 16;                       // row of the padded weights
+  extern __shared__ float smem[];
+  float* ws = smem;                                    // [r][WS], tap v at 15 + v
+  float* xs = smem + r * WS;
+  int bid = blockIdx.x;
+  const int bx = bid % nbx;
+  bid /= nbx;
+  const int by = bid % nby;
+  const int b = bid / nby;
+  const int n = blockIdx.y;
+  const int i0 = by * 16 * WR, j0 = bx * 16 * WC;
+  const int BH = 16 * WR + r - 1;
+  const int sh = VEC == 4 ? -pad & 3 : 0;              // columns staged left of the first
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wr = wave / WC, wc = wave % WC;
+  const int lr = lane & 15, lk = lane >> 4;
+  const size_t plane = (size_t)H * W;
+  const float* __restrict__ xb = x + (size_t)b * (dw ? N : M) * plane + (dw ? (size_t)n * plane : 0);
+  const float* __restrict__ wb = w + (size_t)n * M * r * r;
+
+  // this wave's first output, and the tap rows and steps that reach the image:
+  // the input row of (output row i, tap row u) is i + u - pad, and step s
+  // covers input columns jw - pad + 4 s .. + 3
+  const int iw = i0 + 16 * wr, jw = j0 + 16 * wc;
+  int ulo = pad - iw - 15, uhi = H + pad - iw;
+  ulo = ulo < 0 ? 0 : ulo;
+  uhi = uhi > r ? r : uhi;
+  if (iw >= Ho || jw >= Wo) uhi = 0;
+  const int slo = pad - jw < 0 ? 0 : (pad - jw) / 4;
+  const int shi = (W + pad - jw + 3) / 4;
+
+  floatx4 acc{0.f, 0.f, 0.f, 0.f};
+  for (int m = 0; m < M; ++m) {
+    if (m) __syncthreads();
+    stage_box<VEC>(xb + (size_t)m * plane, plane, 1, xs, 1, BH, BH, BW, H, W, i0 - pad,
+                   j0 - pad - sh);
+    // a wave per tap row
+    for (int u = wave; u < r; u += 4) {
+      const __amdgpu_buffer_rsrc_t rs = read_rsrc(wb + (size_t)m * r * r + u * r, 4u * r);
+      if (lane < WS) copy_lds(rs, ws + u * WS, 4u * (unsigned)(lane - 15));
+    }
+    copies_done();
+    const float* xa = xs + (16 * wr + lr) * BW + 16 * wc + lk + sh;
+    const float* wa = ws + 15 + lk - lr;
+    floatx4 sum{0.f, 0.f, 0.f, 0.f};
+    for (int u = ulo; u < uhi; ++u) {
+      float bf[S], af[S];
+#pragma unroll
+      for (int s = 0; s < S; ++s) {
+        bf[s] = wa[u * WS + 4 * s];
+        af[s] = xa[u * BW + 4 * s];
+      }
+      floatx4 part{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int s = 0; s < S; ++s) {
+        if (s < slo || s >= shi) continue;
+        part = __builtin_amdgcn_mfma_f32_16x16x4f32(af[s], bf[s], part, 0, 0, 0);
+      }
+      sum += part;
+    }
+    acc += sum;
+  }
+  float* __restrict__ yb = y + ((size_t)b * N + n) * Ho * Wo;
+  const int col = jw + lr;
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    const int row = iw + 4 * lk + v;
+    if (row < Ho && col < Wo) yb[(size_t)row * Wo + col] = acc[v];
+  }
+}
+
+// ---- depthwise / few output channels, small kernels -------------------------
+// A lane computes 4 columns of a row of NB output channels.  Work-group: SP
+// sub-blocks of TS lanes on the same outputs, each summing its share of the
+// input channels (added through LDS at the end); CG lanes across, RG rows of
+// lanes (RG CG <= TS, the other lanes only copy).  The taps are scalars
+// (uniform loads).
+template <int R, int NB, int VEC>
+__global__ __launch_bounds__(512) void direct_valu(
+    const float* __restrict__ x, const float* __restrict__ w, float* __restrict__ y, int M, int N,
+    int dw, int H, int W, int pad, int Ho, int Wo, int TS, int CG, int RG, int MCH, int nbx,
+    int nby, int BW, int vec) {
+  // columns staged left of a lane's first (VEC = 4 takes pad = (R - 1) / 2), and
+  // the columns it reads, in quads
+  constexpr int SH = VEC == 4 ? -((R - 1) / 2) & 3 : 0;
+  constexpr int NX = (SH + R + 3 + 3) / 4 * 4;
+  extern __shared__ float smem[];
+  int bid = blockIdx.x;
+  const int bx = bid % nbx;
+  bid /= nbx;
+  const int by = bid % nby;
+  const int b = bid / nby;
+  const int n0 = blockIdx.y * NB;
+  const int SP = blockDim.x / TS;
+  const int sub = SP > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x / TS) : 0;
+  const int t = threadIdx.x - sub * TS;
+  const int ty = t / CG, tx = t - ty * CG;
+  const bool own = ty < RG;
+  const int i0 = by * RG, j0 = bx * 4 * CG;
+  const int BH = RG + R - 1, CS = BH * BW;
+  const size_t plane = (size_t)H * W;
+  const float* __restrict__ xb =
+      x + (size_t)b * (dw ? N : M) * plane + (dw ? (size_t)n0 * plane : 0);
+
+  float acc[NB][4];
+#pragma unroll
+  for (int k = 0; k < NB; ++k)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc[k][j] = 0.0f;
+
+  for (int m0 = 0; m0 < M; m0 += SP * MCH) {
+    if (m0) __syncthreads();
+    const int left = M - m0, nch = left < SP * MCH ? left : SP * MCH;
+    stage_box<VEC>(xb + (size_t)m0 * plane, plane, nch, smem, nch, BH, BH, BW, H, W, i0 - pad,
+                   j0 - pad - SH);
+    copies_done();
+    for (int mi = sub; mi < nch; mi += SP) {
+      const float* xa = smem + mi * CS + (own ? ty * BW + 4 * tx : 0);
+      const float* __restrict__ wm[NB];
+#pragma unroll
+      for (int k = 0; k < NB; ++k) {
+        // channels past the last one repeat it (not stored)
+        const int n = n0 + k < N ? n0 + k : N - 1;
+        wm[k] = w + ((size_t)n * M + m0 + mi) * (R * R);
+      }
+      // a channel's sum, of its tap rows' sums from 6 x 6 on
+      constexpr int UR = R >= 6 ? 1 : R;
+      float sum[NB][4];
+#pragma unroll
+      for (int k = 0; k < NB; ++k)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) sum[k][j] = 0.0f;
+#pragma unroll
+      for (int u0 = 0; u0 < R; u0 += UR) {
+        float part[NB][4];
+#pragma unroll
+        for (int k = 0; k < NB; ++k)
+#pragma unroll
+          for (int j = 0; j < 4; ++j) part[k][j] = 0.0f;
+#pragma unroll
+        for (int u = u0; u < u0 + UR; ++u) {
+          float xv[NX];
+#pragma unroll
+          for (int c = 0; c < NX; c += 4) {
+            const float4 v = *reinterpret_cast<const float4*>(xa + u * BW + c);
+            xv[c] = v.x;  xv[c + 1] = v.y;  xv[c + 2] = v.z;  xv[c + 3] = v.w;
+          }
+#pragma unroll
+          for (int v = 0; v < R; ++v)
+#pragma unroll
+            for (int k = 0; k < NB; ++k) {
+              const float c = wm[k][u * R + v];
+#pragma unroll
+              for (int j = 0; j < 4; ++j) part[k][j] = fmaf(c, xv[SH + v + j], part[k][j]);
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < NB; ++k)
+#pragma unroll
+          for (int j = 0; j < 4; ++j) sum[k][j] += part[k][j];
+      }
+#pragma unroll
+      for (int k = 0; k < NB; ++k)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc[k][j] += sum[k][j];
+    }
+  }
+  if (SP > 1) {
+    // sub-blocks 1 .. SP-1 hand their sums to sub-block 0, one value of every
+    // lane at a time (consecutive lanes side by side)
+    constexpr int NV = NB * 4;
+    __syncthreads();
+    if (sub > 0) {
+#pragma unroll
+      for (int e = 0; e < NV; ++e)
+        smem[((sub - 1) * NV + e) * TS + t] = acc[e / 4][e % 4];
+    }
+    __syncthreads();
+    if (sub > 0) return;
+    for (int s = 0; s < SP - 1; ++s)
+#pragma unroll
+      for (int e = 0; e < NV; ++e)
+        acc[e / 4][e % 4] += smem[(s * NV + e) * TS + t];
+  }
+  if (!own) return;
+  const size_t oplane = (size_t)Ho * Wo;
+  const int col = j0 + 4 * tx;
+#pragma unroll
+  for (int k = 0; k < NB; ++k) {
+    if (n0 + k >= N) break;
+    float* __restrict__ yb = y + ((size_t)b * N + n0 + k) * oplane;
+    const int row = i0 + ty;
+    if (row >= Ho) continue;
+    float* yr = yb + (size_t)row * Wo;
+    if (vec && col + 3 < Wo) {
+      *reinterpret_cast<float4*>(yr + col) =
+          make_float4(acc[k][0], acc[k][1], acc[k][2], acc[k][3]);
+    } else {
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        if (col + j < Wo) yr[col + j] = acc[k][j];
+    }
+  }
+}
+
+// ---- small dense layers -----------------------------------------------------
+// D[n][px] += sum over (m, u, v) of w[n][m][u][v] x[m][row + u][col + v]: A is
+// 16 output channels x 4 of the products, B the same 4 x 16 pixels of a row.
+// The 4 products of a step are 4 input channels at one tap (KV = 0), or, with
+// few input channels, 4 neighbouring taps of a row (KV = 1).  A run is the
+// steps of one tap row (of one channel or group of 4); its operands are read
+// together.  Work-group: 8 waves on pixel tiles (16 columns of a row each, PC
+// tiles across) x 16 NA channels; WK waves share a tile's sums (each takes
+// every WK-th run), and each of the other 8 / WK has NP tiles of its own.
+template <int R, int NA, int NP, int KV, int VEC>
+__global__ __launch_bounds__(512) void direct_mfma(
+    const float* __restrict__ x, const float* __restrict__ w, float* __restrict__ y, int M, int N,
+    int H, int W, int pad, int Ho, int Wo, int WK, int PC, int PR, int MCH, int nbx, int nby,
+    int BW, int BHC, int w4) {
+  constexpr int RR = R * R;
+  constexpr int R4 = (R + 3) / 4 * 4;
+  constexpr int MS = KV ? R * R4 : (RR | 1);           // weights of a channel, odd with KV = 0
+  constexpr int STEPS = KV ? R4 / 4 : R;               // steps of a run
+  constexpr int SV = KV ? 4 : 1;                       // columns from step to step
+  extern __shared__ float smem[];
+  const int NS = (MCH * MS + 255) / 256 * 256 + 4;     // weights of an output channel
+  int bid = blockIdx.x;
+  const int bx = bid % nbx;
+  bid /= nbx;
+  const int by = bid % nby;
+  const int b = bid / nby;
+  const int n0 = blockIdx.y * 16 * NA;
+  const int i0 = by * PR, j0 = bx * 16 * PC;
+  const int BH = PR + R - 1, CS = BHC * BW;
+  const int sh = VEC == 4 ? -pad & 3 : 0;              // columns staged left of the first
+  float* wsm = smem;                                   // [n][m][tap], strides NS, MS
+  float* xs = smem + 16 * NA * NS;                     // [m][row][col], strides CS, BW
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wk = wave % WK, wp = wave / WK;
+  const int lr = lane & 15, lk = lane >> 4;
+  const size_t plane = (size_t)H * W;
+
+  floatx4 acc[NA][NP];
+#pragma unroll
+  for (int a = 0; a < NA; ++a)
+#pragma unroll
+    for (int p = 0; p < NP; ++p) acc[a][p] = floatx4{0.f, 0.f, 0.f, 0.f};
+  // this lane's place in the box of pixel tile p, and in the weights
+  int bo[NP];
+#pragma unroll
+  for (int p = 0; p < NP; ++p) {
+    const int tile = wp * NP + p;
+    bo[p] = (tile / PC) * BW + (tile % PC) * 16 + sh + lr + (KV ? lk : lk * CS);
+  }
+  const int ao = lr * NS + (KV ? lk : lk * MS);
+
+  for (int m0 = 0; m0 < M; m0 += MCH) {
+    if (m0) __syncthreads();
+    const int left = M - m0, nch = left < MCH ? left : MCH;
+    const int mpad = KV ? nch : (nch + 3) / 4 * 4;
+    // weights of the chunk: a wave per output channel; zero for channels past
+    // M or N and (KV) for the taps that fill a row up to R4
+    for (int n = wave; n < 16 * NA; n += 8) {
+      const bool live = n0 + n < N;
+      const __amdgpu_buffer_rsrc_t rs =
+          read_rsrc(w + ((size_t)(live ? n0 + n : 0) * M + m0) * RR, live ? 4u * nch * RR : 0u);
+      float* d = wsm + n * NS;
+      if (!KV && MS == RR && w4) {
+        // 16-byte aligned rows of whole quads
+        for (int i = 0; i < mpad * MS; i += 256) copy_lds<16>(rs, d + i, 4u * (i + 4 * lane));
+      } else {
+        for (int i = 0; i < mpad * MS; i += 64) {
+          const int e = i + lane, m = e / MS, t = e - m * MS;
+          unsigned off;
+          if (KV) {
+            const int u = t / R4, v = t - u * R4;
+            off = v < R ? 4u * (unsigned)(m * RR + u * R + v) : kOutside;
+          } else {
+            off = t < RR ? 4u * (unsigned)(m * RR + t) : kOutside;
+          }
+          copy_lds(rs, d + i, off);
+        }
+      }
+    }
+    stage_box<VEC>(x + ((size_t)b * M + m0) * plane, plane, nch, xs, mpad, BH, BHC, BW, H, W,
+                   i0 - pad, j0 - pad - sh);
+    copies_done();
+    floatx4 part[NA][NP];
+#pragma unroll
+    for (int a = 0; a < NA; ++a)
+#pragma unroll
+      for (int p = 0; p < NP; ++p) part[a][p] = floatx4{0.f, 0.f, 0.f, 0.f};
+    const int runs = (KV ? mpad : mpad / 4) * R;
+    for (int o = wk, k = 0; o < runs; o += WK) {
+      const int mg = o / R, u = o - mg * R;
+      const float* ap = wsm + ao + (KV ? mg * MS + u * R4 : 4 * mg * MS + u * R);
+      const float* bp = xs + (KV ? mg : 4 * mg) * CS + u * BW;
+      float af[STEPS][NA], bf[STEPS][NP];
+#pragma unroll
+      for (int s = 0; s < STEPS; ++s) {
+#pragma unroll
+        for (int a = 0; a < NA; ++a) af[s][a] = ap[16 * a * NS + SV * s];
+#pragma unroll
+        for (int p = 0; p < NP; ++p) bf[s][p] = bp[bo[p] + SV * s];
+      }
+#pragma unroll
+      for (int s = 0; s < STEPS; ++s)
+#pragma unroll
+        for (int a = 0; a < NA; ++a)
+#pragma unroll
+          for (int p = 0; p < NP; ++p)
+            part[a][p] =
+                __builtin_amdgcn_mfma_f32_16x16x4f32(af[s][a], bf[s][p], part[a][p], 0, 0, 0);
+      if (++k % (R >= 8 ? 1 : 2) == 0) {
+#pragma unroll
+        for (int a = 0; a < NA; ++a)
+#pragma unroll
+          for (int p = 0; p < NP; ++p) {
+            acc[a][p] += part[a][p];
+            part[a][p] = floatx4{0.f, 0.f, 0.f, 0.f};
+          }
+      }
+    }
+#pragma unroll
+    for (int a = 0; a < NA; ++a)
+#pragma unroll
+      for (int p = 0; p < NP; ++p) acc[a][p] += part[a][p];
+  }
+  if (WK > 1) {
+    // the waves of a tile add their sums through LDS
+    __syncthreads();
+    floatx4* red = reinterpret_cast<floatx4*>(smem);   // [wave][a][p][lane]
+    if (wk > 0) {
+#pragma unroll
+      for (int a = 0; a < NA; ++a)
+#pragma unroll
+        for (int p = 0; p < NP; ++p) red[((wave * NA + a) * NP + p) * 64 + lane] = acc[a][p];
+    }
+    __syncthreads();
+    if (wk > 0) return;
+    for (int k = 1; k < WK; ++k)
+#pragma unroll
+      for (int a = 0; a < NA; ++a)
+#pragma unroll
+        for (int p = 0; p < NP; ++p)
+          acc[a][p] += red[(((wave + k) * NA + a) * NP + p) * 64 + lane];
+  }
+  const size_t oplane = (size_t)Ho * Wo;
+#pragma unroll
+  for (int p = 0; p < NP; ++p) {
+    const int tile = wp * NP + p;
+    const int row = i0 + tile / PC, col = j0 + (tile % PC) * 16 + lr;
+    if (row >= Ho || col >= Wo) continue;
+#pragma unroll
+    for (int a = 0; a < NA; ++a)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int n = n0 + 16 * a + 4 * lk + v;
+        if (n < N) y[((size_t)b * N + n) * oplane + (size_t)row * Wo + col] = acc[a][p][v];
+      }
+  }
+}
+
+// The plain weights into the plan's buffer.
+__global__ __launch_bounds__(256) void direct_weights(const float* __restrict__ w,
+                                                      float* __restrict__ U, size_t n) {
+  const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
+  if (i < n) U[i] = w[i];
+}
+
+// ---- launches ---------------------------------------------------------------
+
+// fixes a runtime integer as a template argument: f(integral constant v) for
+// the v in [LO, HI] that equals `value`
+template <int LO, int HI, class F>
+hipError_t with_int(int value, F&& f) {
+  if constexpr (LO > HI) {
+    return hipErrorInvalidValue;
+  } else {
+    if (value == LO) return f(std::integral_constant<int, LO>{});
+    return with_int<LO + 1, HI>(value, std::forward<F>(f));
+  }
+}
+
+template <class K>
+hipError_t lds_limit(K kernel, size_t bytes) {
+  if (bytes <= 64 * 1024) return hipSuccess;
+  return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
+                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+}
+
+}  // namespace
+
+// which kernels exist: toeplitz r = 12..31; valu r = 2..13 with one output
+// channel a lane, 2..9 with more; mfma r = 2..15, or 2..9 with steps of a
+// tap row
+hipError_t launch_direct(const nwg_plan_info& g, const DirectShape& d, const float* x,
+                         const float* w, float* y, hipStream_t s) {
+  const int M = g.depthwise ? 1 : g.M;
+  const bool v4 = g.W % 4 == 0;
+  constexpr std::integral_constant<int, 1> one{};
+  constexpr std::integral_constant<int, 4> four{};
+  if (d.kind == kDirectToeplitz) {
+    const int WR = d.wr, WC = 4 / d.wr;
+    const int S = (g.r + 15 + 3) / 4;
+    const int nbx = (g.Wo + 16 * WC - 1) / (16 * WC), nby = (g.Ho + 16 * WR - 1) / (16 * WR);
+    const int BW = direct_toeplitz_row(g.r, WC), BH = 16 * WR + g.r - 1;
+    const size_t lds = ((size_t)g.r * (4 * S + 16) + (size_t)BH * BW) * sizeof(float);
+    const dim3 grid((unsigned)((long long)nbx * nby * g.B), (unsigned)g.N);
+    return with_int<7, 12>(S, [&](auto s_) {
+      auto go = [&](auto v_) {
+        auto k = direct_toeplitz<decltype(s_)::value, decltype(v_)::value>;
+        const hipError_t e = lds_limit(k, lds);
+        if (e != hipSuccess) return e;
+        k<<<grid, 256, lds, s>>>(x, w, y, M, g.N, g.depthwise, g.r, g.H, g.W, g.pad, g.Ho, g.Wo,
+                                 WR, WC, nbx, nby, BW);
+        return hipGetLastError();
+      };
+      return v4 ? go(four) : go(one);
+    });
+  }
+  if (d.kind == kDirectValu) {
+    const int NB = d.nb, TS = d.ts, SP = d.sp, CG = d.cg, RG = TS / CG;
+    const int nbx = (g.Wo + 4 * CG - 1) / (4 * CG), nby = (g.Ho + RG - 1) / RG;
+    const bool vx = v4 && 2 * g.pad == g.r - 1;
+    const int sh = vx ? -g.pad & 3 : 0;
+    const int BW = 4 * CG - 4 + (sh + g.r + 6) / 4 * 4, BH = RG + g.r - 1;
+    size_t lds = (size_t)SP * d.mch * BH * BW;
+    if ((size_t)(SP - 1) * NB * 4 * TS > lds) lds = (size_t)(SP - 1) * NB * 4 * TS;
+    lds *= sizeof(float);
+    const int vec = g.Wo % 4 == 0;                     // y is 16-byte aligned, so every row then is
+    const dim3 grid((unsigned)((long long)nbx * nby * g.B), (unsigned)((g.N + NB - 1) / NB));
+    return with_int<2, 13>(g.r, [&](auto r_) {
+      return with_int<1, 4>(NB, [&](auto n_) {
+        constexpr int R = decltype(r_)::value, NBC = decltype(n_)::value;
+        if constexpr (NBC > 1 && R > 9) {
+          return hipErrorInvalidValue;
+        } else {
+          auto go = [&](auto v_) {
+            auto k = direct_valu<R, NBC, decltype(v_)::value>;
+            const hipError_t e = lds_limit(k, lds);
+            if (e != hipSuccess) return e;
+            k<<<grid, TS * SP, lds, s>>>(x, w, y, M, g.N, g.depthwise, g.H, g.W, g.pad, g.Ho, g.Wo,
+                                         TS, CG, RG, d.mch, nbx, nby, BW, vec);
+            return hipGetLastError();
+          };
+          return vx ? go(four) : go(one);
+        }
+      });
+    });
+  }
+  if (d.kind == kDirectMfma) {
+    const int PR = d.np * (8 / d.wk) / d.pc;
+    const int nbx = (g.Wo + 16 * d.pc - 1) / (16 * d.pc), nby = (g.Ho + PR - 1) / PR;
+    const DirectBox bx = direct_mfma_box(g, d);
+    const size_t lds = direct_mfma_lds(g, d);
+    const int w4 = g.M % 4 == 0;
+    const dim3 grid((unsigned)((long long)nbx * nby * g.B),
+                    (unsigned)((g.N + 16 * d.na - 1) / (16 * d.na)));
+    return with_int<2, 15>(g.r, [&](auto r_) {
+      return with_int<0, 1>(d.kv, [&](auto kv_) {
+        constexpr int R = decltype(r_)::value, KV = decltype(kv_)::value;
+        auto go = [&](auto na_, auto np_, auto v_) {
+          auto k = direct_mfma<R, decltype(na_)::value, decltype(np_)::value, KV,
+                               decltype(v_)::value>;
+          const hipError_t e = lds_limit(k, lds);
+          if (e != hipSuccess) return e;
+          k<<<grid, 512, lds, s>>>(x, w, y, g.M, g.N, g.H, g.W, g.pad, g.Ho, g.Wo, d.wk, d.pc, PR,
+                                   d.mch, nbx, nby, bx.row, bx.rows, w4);
+          return hipGetLastError();
+        };
+        constexpr std::integral_constant<int, 2> two{};
+        if constexpr (KV == 1) {
+          if constexpr (R > 9)
+            return hipErrorInvalidValue;
+          else if (d.na == 2 && d.np == 4)
+            return v4 ? go(two, four, four) : go(two, four, one);
+          else if (d.na == 1 && d.np == 2)
+            return v4 ? go(one, two, four) : go(one, two, one);
+          else
+            return hipErrorInvalidValue;
+        } else {
+          if (d.na != 1 || d.np != 2) return hipErrorInvalidValue;
+          return v4 ? go(one, two, four) : go(one, two, one);
+        }
+      });
+    });
+  }
+  return hipErrorInvalidValue;
+}
+
+hipError_t launch_direct_weights(const nwg_plan_info& g, const float* w, float* U, hipStream_t s) {
+  const size_t n = (size_t)g.N * (g.depthwise ? 1 : g.M) * g.r * g.r;
+  direct_weights<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(w, U, n);
+  return hipGetLastError();
+}
+
+}  // namespace nwg

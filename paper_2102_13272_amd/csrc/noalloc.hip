@@ -7,6 +7,7 @@
 #include <cstdint>
 #include <mutex>
 
+#include "direct.h"
 #include "nwg_internal.h"
 
 namespace {
@@ -84,6 +85,11 @@ extern "C" int nwg_conv2d_noalloc(int B, int M, int N, int H, int W, int r, int 
     if (sdev != cur)
       return nwg::fail(NWG_EINVAL, "the stream runs on device %d, device %d is current", sdev,
                        cur);
+  }
+  if (tile == NWG_TILE_AUTO) {
+    // the plan's choice; no scratch
+    const nwg::DirectShape d = nwg::direct_route(g);
+    if (d.kind != nwg::kDirectNone) return nwg::direct_conv(g, d, x, w, y, s);
   }
   unsigned char* base = nullptr;
   rc = scratch_of_current_device(&base);

@@ -12,6 +12,7 @@
 #include <string>
 #include <vector>
 
+#include "direct.h"
 #include "nwg_internal.h"
 
 namespace {
@@ -33,6 +34,7 @@ struct nwg_plan {
   float* Yh = nullptr;
   const float* cached_w = nullptr;
   bool weights_valid = false;
+  nwg::DirectShape direct;      // NWG_TILE_AUTO plans whose layer runs direct
   bool timing = false;
   std::vector<TimingRecord> pending;
   std::vector<hipEvent_t> event_pool;
@@ -250,10 +252,20 @@ int run_pipelined(nwg_plan* p, const float* x, hipStream_t s) {
   return rc != NWG_OK ? rc : rw;
 }
 
-int run_kernel_transform(nwg_plan* p, const nwg_plan_info& g, const float* w, float* U,
-                         hipStream_t s) {
-  return timed(p, 0, s, "kernel transform launch",
-               [&] { return launch_kxform(g, w, U, s); });
+// Whether nwg_conv2d runs the plan's layer direct: not in the precision or the
+// pipeline that only the nest has.
+bool runs_direct(const nwg_plan* p) {
+  return p->direct.kind != nwg::kDirectNone && p->info.precision == NWG_PRECISION_FP32 &&
+         p->info.pipeline_parts <= 1;
+}
+
+// The weights as nwg_conv2d reads them, into the plan's U: transformed, or
+// plain where the layer runs direct.
+int run_kernel_transform(nwg_plan* p, const float* w, hipStream_t s) {
+  return timed(p, 0, s, "kernel transform launch", [&] {
+    return runs_direct(p) ? nwg::launch_direct_weights(p->info, w, p->U, s)
+                          : launch_kxform(p->info, w, p->U, s);
+  });
 }
 
 // A plan's buffers: U (transformed weights), V and Z (with the partial sums
@@ -322,7 +334,7 @@ int run_steps(nwg_plan* p, const nwg_plan_info& g, const Workspace& ws, const fl
 
 namespace {
 
-nwg_plan* create_plan(const nwg_plan_info& g) {
+nwg_plan* create_plan(const nwg_plan_info& g, int tile) {
   if (nwg::check_plan_request(g) != NWG_OK) return nullptr;
   nwg_plan* p = new (std::nothrow) nwg_plan;
   if (!p) {
@@ -330,6 +342,7 @@ nwg_plan* create_plan(const nwg_plan_info& g) {
     return nullptr;
   }
   p->info = g;
+  if (tile == NWG_TILE_AUTO) p->direct = nwg::direct_route(g);
   if (hipGetDevice(&p->device) != hipSuccess) {
     hipGetLastError();
     fail(NWG_EHIP, "no HIP device available");
@@ -369,6 +382,11 @@ int kernel_transform_into(const nwg_plan_info& g, const float* w, float* U, hipS
   return check_launch(launch_kxform(g, w, U, s), "kernel transform launch", s);
 }
 
+int direct_conv(const nwg_plan_info& g, const DirectShape& d, const float* x, const float* w,
+                float* y, hipStream_t s) {
+  return check_launch(launch_direct(g, d, x, w, y, s), "direct convolution launch", s);
+}
+
 int conv_steps(const nwg_plan_info& g, const float* U, float* V, float* Yh, const float* x,
                float* y, hipStream_t s) {
   return run_steps(nullptr, g, {U, V, Yh}, x, y, s);
@@ -381,13 +399,13 @@ extern "C" {
 nwg_plan* nwg_plan_create_pad(int B, int M, int N, int H, int W, int r, int pad, int tile) {
   nwg_plan_info g;
   if (nwg::compute_geometry(B, M, N, H, W, r, pad, tile, 0, &g) != NWG_OK) return nullptr;
-  return create_plan(g);
+  return create_plan(g, tile);
 }
 
 nwg_plan* nwg_plan_create_depthwise(int B, int C, int H, int W, int r, int pad, int tile) {
   nwg_plan_info g;
   if (nwg::compute_geometry(B, C, C, H, W, r, pad, tile, 1, &g) != NWG_OK) return nullptr;
-  return create_plan(g);
+  return create_plan(g, tile);
 }
 
 nwg_plan* nwg_plan_create(int B, int M, int N, int H, int W, int r, int tile) {
@@ -416,6 +434,8 @@ int nwg_plan_query(const nwg_plan* p, nwg_plan_info* out) {
   *out = p->info;
   return NWG_OK;
 }
+
+int nwg_plan_direct(const nwg_plan* p) { return p && runs_direct(p) ? 1 : 0; }
 
 int nwg_kernel_transform(const nwg_plan* p, const float* w, float* U, void* stream) {
   if (!p || !w || !U)
@@ -475,7 +495,7 @@ int nwg_plan_set_weights(nwg_plan* p, const float* w, void* stream) {
     return fail(NWG_EINVAL, "NULL argument to nwg_plan_set_weights");
   const int rd = check_plan_device(p, (hipStream_t)stream);
   if (rd != NWG_OK) return rd;
-  const int rc = run_kernel_transform(p, p->info, w, p->U, (hipStream_t)stream);
+  const int rc = run_kernel_transform(p, w, (hipStream_t)stream);
   if (rc == NWG_OK) {
     p->cached_w = w;
     p->weights_valid = true;
@@ -494,6 +514,10 @@ int nwg_conv2d(nwg_plan* p, const float* x, const float* w, float* y, void* stre
     const int rc = nwg_plan_set_weights(p, w, stream);
     if (rc != NWG_OK) return rc;
   }
+  if (runs_direct(p))
+    return timed(p, 2, (hipStream_t)stream, "direct convolution launch", [&] {
+      return nwg::launch_direct(p->info, p->direct, x, p->U, y, (hipStream_t)stream);
+    });
   return run_steps(p, p->info, {p->U, p->V, p->Yh}, x, y, (hipStream_t)stream);
 }
 

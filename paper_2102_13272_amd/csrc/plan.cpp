@@ -549,6 +549,200 @@ int check_plan_request(const nwg_plan_info& g) {
   return NWG_OK;
 }
 
+// ---- direct kernels ----------------------------------------------------------
+
+int direct_toeplitz_row(int r, int wc) {
+  // 16 wc + r - 1 columns in whole steps of 4, 3 more for an aligned start, as
+  // 4 x an odd number (the 16 rows of a fragment in 16 bank quads)
+  const int S = (r + 15 + 3) / 4;
+  return 4 * ((16 * wc - 16 + 4 * S + 3 + 3) / 4 | 1);
+}
+
+DirectBox direct_mfma_box(const nwg_plan_info& g, const DirectShape& d) {
+  const int PR = d.np * (8 / d.wk) / d.pc;
+  const bool v4 = g.W % 4 == 0;
+  const int rows = PR + g.r - 1;
+  int row = 16 * d.pc + (d.kv ? (g.r + 3) / 4 * 4 : g.r - 1) + (v4 ? -g.pad & 3 : 0);
+  if (v4) row = (row + 3) / 4 * 4;
+  if (d.kv) return {row, rows};
+  // the smallest box with a channel stride of 16 x an odd number of values: the
+  // 4 channels of a fragment in 4 different quarters of the banks
+  DirectBox best{0, 0};
+  for (int bw = row; bw < row + 16; bw += v4 ? 4 : 1)
+    for (int bh = rows; bh < rows + 16; ++bh)
+      if (bw * bh % 32 == 16 && (best.row == 0 || bw * bh < best.row * best.rows)) best = {bw, bh};
+  return best;
+}
+
+size_t direct_mfma_lds(const nwg_plan_info& g, const DirectShape& d) {
+  const int rr = g.r * g.r, r4 = (g.r + 3) / 4 * 4;
+  const int MS = d.kv ? g.r * r4 : (rr | 1);
+  const size_t NS = ((size_t)d.mch * MS + 255) / 256 * 256 + 4;
+  const DirectBox b = direct_mfma_box(g, d);
+  size_t v = 16 * d.na * NS + (size_t)d.mch * b.row * b.rows;
+  const size_t red = (size_t)8 * d.na * d.np * 64 * 4;    // the waves' sums of a tile
+  if (d.wk > 1 && v < red) v = red;
+  return v * sizeof(float);
+}
+
+namespace {
+
+constexpr size_t kLds = 160 * 1024;       // of a CU
+
+long long ceil_div(long long a, long long b) { return (a + b - 1) / b; }
+
+// Every direct kernel addresses the planes it stages at once with 32-bit byte
+// offsets (with the rows and columns around them that the padding adds), and
+// keeps the plain weights in the plan's U.
+bool direct_fits(const nwg_plan_info& g, const DirectShape& d) {
+  const double rows = (double)g.H + 2.0 * g.pad + 128.0, cols = (double)g.W + 2.0 * g.pad + 128.0;
+  if (rows * cols * d.mch * d.sp * 4.0 >= 2147483648.0) return false;
+  if (g.N > 65535 || (double)g.B * (g.Ho / 4 + 1.0) * (g.Wo / 16 + 1.0) >= 2147483648.0)
+    return false;
+  const double Mk = g.depthwise ? 1 : g.M;
+  return 4.0 * g.N * Mk * g.r * g.r <= (double)g.u_bytes;
+}
+
+// Microseconds of a dense plan's nest: its launches, the serial chain over the
+// contraction's channels, and what its kernels read and write (U once, V and Z
+// twice, with the live groups' share) at 4.2 (depth 1-2) or 5 TB/s; x and y at
+// 2.5 TB/s in the single kernels.  Fitted to
+// 350 layers of 1..240 channels and 2..15 taps on maps of 8..256 values a side
+// (most within a third).
+double nest_us(const nwg_plan_info& g) {
+  const bool f33 = g.tile == NWG_TILE_F3X3_3X3;
+  if (g.fused_input && !f33) {
+    const double serial = (g.n == 3 ? 1.5 : 2.2) * g.M, all = (double)g.P * g.T * g.M / 2e6;
+    return (g.n == 3 ? 18.0 : 88.0) + (serial > all ? serial : all);
+  }
+  const double live = !f33 && g.n >= 3 ? (double)g.live_groups / (double)(g.P / 16) : 1.0;
+  const double base = g.fused_conv ? 5.0 + 0.6 * g.M
+                      : f33        ? (g.n == 1 ? 20.0 : 32.0)
+                                   : (g.n == 1 ? 9.0 : g.n == 2 ? 11.0 : g.n == 3 ? 18.0 : 95.0);
+  double b = 4.0 * g.B * ((double)g.M * g.H * g.W + (double)g.N * g.Ho * g.Wo);
+  if (!g.fused_conv) {
+    b += live * (double)g.u_bytes + 2.0 * live * (double)g.yhat_bytes;
+    if (!g.fused_input) b += 2.0 * live * (double)g.v_bytes;
+  }
+  const double chain = f33 || g.fused_conv ? 0.0 : 0.12 * g.M;
+  return base + chain + b / (g.fused_conv ? 2.5e6 : f33 || g.n < 3 ? 4.2e6 : 5.0e6);
+}
+
+// Microseconds of the direct kernels, from the same layers: a launch, then the
+// longer of their arithmetic (whole blocks and tiles; the smaller the kernel,
+// the more of the time goes to the staging) and the serial chain over the input
+// channels of one work-group.
+double direct_mfma_us(const nwg_plan_info& g, const DirectShape& d) {
+  const double flop = 2.0 * g.B * 16.0 * ceil_div(g.N, 16) * (d.kv ? g.M : 4.0 * ceil_div(g.M, 4)) *
+                      (double)g.Ho * 16.0 * d.pc * ceil_div(g.Wo, 16 * d.pc) * g.r * g.r;
+  double rate = 110e6 * g.r / (g.r + 3.3);                // FLOP a microsecond
+  double chain = g.M * (0.05 + 0.003 * g.r * g.r);
+  if (g.r >= 10) rate *= g.r >= 14 ? 0.65 : g.r >= 12 ? 0.8 : 0.9;   // (few channels fit a stage)
+  if (!d.kv && (g.r % 2 == 0 || g.M % 4)) {                          // taps copied 4 bytes at a time, not 16
+    rate *= 0.75;
+    chain *= 1.3;
+  }
+  // a tap row's few steps overlap the stores of y, with few channels most of the time
+  const double mm = d.kv ? 0.5 * flop / rate : flop / rate;
+  return 4.5 + (mm > chain ? mm : chain) +
+         4.0 * g.B * g.N * (double)g.Ho * g.Wo / 4.2e6;
+}
+
+double direct_valu_us(const nwg_plan_info& g, const DirectShape& d) {
+  const double flop = 2.0 * g.B * d.nb * ceil_div(g.N, d.nb) * (double)g.M *
+                      (8.0 * ceil_div(g.Ho, 8)) * (32.0 * ceil_div(g.Wo, 32)) * g.r * g.r;
+  const double chain = ceil_div(g.M, d.sp) * (0.5 + 0.035 * g.r * g.r);
+  return 4.5 + (flop / 40e6 > chain ? flop / 40e6 : chain);
+}
+
+double direct_toeplitz_us(const nwg_plan_info& g, const DirectShape& d) {
+  const int rows = 16 * d.wr, cols = 64 / d.wr;
+  const double flop = 2.0 * g.B * g.N * (double)g.M * rows * ceil_div(g.Ho, rows) * cols *
+                      ceil_div(g.Wo, cols) * g.r * g.r;
+  const double rate = 110e6 * g.r / (g.r + 15.0), chain = g.M * (0.2 + 0.3 * g.r);
+  return 4.5 + (flop / rate > chain ? flop / rate : chain);
+}
+
+}  // namespace
+
+DirectShape direct_shape(const nwg_plan_info& g, DirectKind kind) {
+  DirectShape d;
+  const int Mk = g.depthwise ? 1 : g.M;
+  if (kind == kDirectToeplitz) {
+    if (g.r < 12 || g.r > 31) return d;
+    // the waves' places with the fewest outputs past the map
+    double best = 0.0;
+    for (int wr = 1; wr <= 4; wr *= 2) {
+      const double a = 16.0 * wr * ceil_div(g.Ho, 16 * wr) * 16.0 * (4 / wr) * ceil_div(g.Wo, 16 * (4 / wr));
+      if (best == 0.0 || a < 0.97 * best) {
+        best = a;
+        d.wr = wr;
+      }
+    }
+  } else if (kind == kDirectValu) {
+    if (g.r < 2 || g.r > 13) return d;
+    if (g.depthwise) {
+      d.ts = 256;
+      d.cg = g.Wo > 32 && (g.Wo + 63) / 64 * 64 <= (g.Wo + 31) / 32 * 32 ? 16 : 8;
+    } else {
+      if (g.N > 8 || (g.r > 9 && g.N > 1)) return d;
+      // 5 = 3 + 2 output channels a lane, 8 = 4 + 4
+      d.nb = g.N <= 4 ? g.N : g.N <= 6 ? 3 : 4;
+      d.sp = g.M >= 32 ? 8 : g.M >= 8 ? 4 : 1;
+      d.mch = d.sp > 1 ? 2 : Mk < 8 ? Mk : 8;
+    }
+  } else if (kind == kDirectMfma) {
+    if (g.depthwise || g.r < 2 || g.r > 15) return d;
+    d.kv = g.M <= 2 && g.r <= 9;
+    // two pixel tiles of a wave side by side, unless a column of tiles then lies
+    // past the map
+    d.pc = ceil_div(g.Wo, 16) % 2 == 1 && g.Wo <= 112 ? 1 : 2;
+    // units of two pixel tiles x 16 channels: as many waves a tile as leave
+    // about a work-group a CU
+    const double units = 0.5 * g.B * g.Ho * d.pc * ceil_div(g.Wo, 16 * d.pc) * ceil_div(g.N, 16);
+    d.wk = units >= 1100 ? 1 : units >= 300 ? 4 : 8;
+    if (d.kv && d.wk == 1 && units >= 8192 && g.N > 16) {
+      d.na = 2;
+      d.np = 4;
+    }
+    const double wgs = units * d.wk / 8.0;
+    const size_t room = wgs > 256 ? kLds / 2 - 1024 : kLds - 1024;
+    const int step = d.kv ? 1 : 4, most = d.kv ? g.M : (g.M + 3) / 4 * 4;
+    for (d.mch = most < 32 ? most : 32; d.mch > step && direct_mfma_lds(g, d) > room;) d.mch -= step;
+    if (direct_mfma_lds(g, d) > kLds - 1024) return DirectShape();
+  }
+  d.kind = kind;
+  return direct_fits(g, d) ? d : DirectShape();
+}
+
+// Depthwise: one kernel x -> y for r <= 7 stays the faster one (7x7 8 x 54 x 83
+// x 83: 15.8 us, direct 18); from r = 8 the direct kernels are (8 x 64 x 56 x
+// 56: r = 8 78 -> 14 us, r = 13 74 -> 18, r = 16 523 -> 26, r = 31 525 -> 53),
+// valu up to r = 11 and toeplitz from 12 (both 20 us at 13).  Dense: the
+// kernel whose estimate is shortest; the nest's arithmetic wins back the
+// transforms' traffic and the launches as channels and maps grow (7x7: 32 ->
+// 32, 64 x 64, 17.8 us against 9.4 direct; 64 -> 64, 8 x 56 x 56, 74 against
+// 125).
+DirectShape direct_route(const nwg_plan_info& g) {
+  if (g.n == 0 || g.tile == NWG_TILE_LD_F2X2_3X3) return DirectShape();
+  if (g.depthwise) {
+    if (g.r <= 7) return DirectShape();
+    return direct_shape(g, g.r <= 11 ? kDirectValu : kDirectToeplitz);
+  }
+  DirectShape best;
+  double t = nest_us(g);
+  auto consider = [&](DirectKind kind, double (*us)(const nwg_plan_info&, const DirectShape&)) {
+    const DirectShape d = direct_shape(g, kind);
+    if (d.kind == kDirectNone || us(g, d) >= t) return;
+    best = d;
+    t = us(g, d);
+  };
+  consider(kDirectValu, direct_valu_us);
+  consider(kDirectMfma, direct_mfma_us);
+  consider(kDirectToeplitz, direct_toeplitz_us);
+  return best;
+}
+
 }  // namespace nwg
 
 extern "C" {

@@ -78,4 +78,29 @@ struct GroupMap {
 };
 GroupMap group_map(const nwg_plan_info& g);
 
+// Launch shape of a direct kernel (direct.hip), kDirectNone where the nest is
+// the faster one.
+enum DirectKind { kDirectNone = 0, kDirectToeplitz, kDirectValu, kDirectMfma };
+struct DirectShape {
+  DirectKind kind = kDirectNone;
+  int wr = 1;                   // toeplitz: waves below each other (4 / wr side by side)
+  int nb = 1, ts = 64, sp = 1, cg = 8;   // valu: output channels a lane, lanes of a
+                                // sub-block, sub-blocks, lanes across
+  int na = 1, np = 2, wk = 8, kv = 0, pc = 2;   // mfma: blocks of 16 output channels, pixel
+                                // tiles a wave, waves a tile, steps of a tap row,
+                                // pixel tiles across
+  int mch = 1;                  // input channels staged (valu: per sub-block)
+};
+// The direct kernel NWG_TILE_AUTO takes for a plan's geometry (its rule is at
+// the function), and that kernel's launch shape on its own.
+DirectShape direct_route(const nwg_plan_info& g);
+DirectShape direct_shape(const nwg_plan_info& g, DirectKind kind);
+// LDS of the kernels' staged boxes.
+struct DirectBox {
+  int row, rows;                // values of a row, rows of a channel
+};
+int direct_toeplitz_row(int r, int wc);
+DirectBox direct_mfma_box(const nwg_plan_info& g, const DirectShape& d);
+size_t direct_mfma_lds(const nwg_plan_info& g, const DirectShape& d);
+
 }  // namespace nwg

@@ -66,6 +66,7 @@ SIGNATURES = [
     ("nwg_plan_create_depthwise", _P, [_I] * 7),
     ("nwg_plan_destroy", None, [_P]),
     ("nwg_plan_query", _I, [_P, ctypes.POINTER(nwg_plan_info)]),
+    ("nwg_plan_direct", _I, [_P]),
     ("nwg_conv2d", _I, [_P, _P, _P, _P, _P]),
     ("nwg_plan_set_weights", _I, [_P, _P, _P]),
     ("nwg_kernel_transform", _I, [_P, _P, _P, _P]),
@@ -243,6 +244,11 @@ class Plan:
         if i["mix_planar"]:
             return (i["live_groups"], 9, i["M"], i["T"])
         return (i["P"], i["M"], i["T"]) if self._f33 else (i["P"] // 4, self._mv, i["T"], 4)
+
+    @property
+    def direct(self) -> bool:
+        """whether conv2d runs the layer direct (nwg_plan_direct)"""
+        return bool(self._lib.nwg_plan_direct(self.handle))
 
     @property
     def z_shape(self):

@@ -1,0 +1,103 @@
+"""NWG_TILE_AUTO plans whose layer runs direct, in one kernel x -> y, against the
+fp64 direct oracle and the staged nest of the same plan, at the edges of the
+kernels' tiles: whole outputs, each kernel, widths that are and are not
+multiples of 4, channel counts that are and are not multiples of a block, even
+and odd kernels, padding from none past "same", images smaller than a tile.
+"""
+import numpy as np
+import pytest
+import torch
+
+from oracle.direct import direct_conv2d, direct_depthwise_conv2d
+from paper_2102_13272_amd import nwg
+from paper_2102_13272_amd.workloads import make_case
+from tests.gpu_util import assert_close, dev
+
+pytestmark = pytest.mark.gpu
+
+AUTO = nwg.NWG_TILE_AUTO
+
+
+@pytest.fixture(autouse=True, scope="module")
+def _gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    nwg.load_library()
+
+
+# (B, M, N, H, W, r, pad, depthwise)
+CASES = [
+    # depthwise, scalar taps (r = 8..11): aligned and ragged rows, one output
+    (2, 3, 3, 33, 36, 9, 4, True), (1, 5, 5, 17, 21, 8, 3, True), (1, 2, 2, 11, 11, 11, 0, True),
+    (3, 2, 2, 9, 130, 10, 9, True), (1, 3, 3, 70, 64, 11, 5, True),
+    # depthwise, banded products (r = 12..31): each step count, tile edges, no and wide padding
+    (1, 3, 3, 16, 64, 12, 6, True), (2, 2, 2, 17, 65, 13, 6, True), (1, 2, 2, 40, 19, 14, 0, True),
+    (1, 2, 2, 64, 20, 17, 8, True), (1, 3, 3, 33, 33, 21, 20, True), (2, 3, 3, 28, 28, 25, 12, True),
+    (1, 2, 2, 31, 31, 31, 0, True), (1, 2, 2, 20, 70, 31, 15, True), (1, 2, 2, 56, 56, 29, 28, True),
+    # few output channels, scalar taps: channel groups of 1..4, sub-blocks of 1, 4, 8
+    (4, 5, 5, 160, 160, 3, 1, False), (2, 32, 1, 128, 132, 9, 4, False), (4, 9, 7, 97, 95, 5, 2, False),
+    (4, 8, 8, 130, 98, 4, 0, False), (1, 40, 3, 21, 20, 2, 1, False), (4, 64, 4, 96, 96, 7, 3, False),
+    (2, 33, 1, 128, 127, 13, 6, False), (4, 6, 2, 100, 90, 6, 5, False),
+    # the same forms on small maps (products of blocks of 16 channels)
+    (2, 5, 5, 33, 64, 3, 1, False), (1, 9, 7, 19, 23, 5, 2, False), (1, 33, 1, 24, 31, 13, 6, False),
+    # few channels, banded products of dense layers
+    (1, 2, 5, 40, 40, 15, 7, False), (2, 3, 2, 30, 45, 19, 9, False), (1, 1, 9, 40, 36, 31, 15, False),
+    # dense: one to three blocks of 16 channels, channel groups of 4 and their rests
+    (1, 32, 32, 64, 64, 7, 3, False), (1, 16, 16, 17, 64, 5, 2, False), (2, 7, 17, 23, 30, 4, 1, False),
+    (1, 4, 33, 12, 15, 6, 5, False), (1, 64, 20, 16, 16, 3, 1, False), (1, 16, 16, 40, 40, 10, 4, False),
+    (1, 5, 40, 31, 33, 2, 0, False), (1, 12, 16, 30, 28, 13, 6, False), (1, 8, 48, 20, 50, 15, 7, False),
+    (2, 20, 16, 96, 100, 8, 3, False), (4, 6, 16, 90, 90, 3, 1, False), (1, 36, 16, 9, 9, 9, 8, False),
+    # dense with steps of a tap row (one or two input channels)
+    (1, 1, 32, 33, 35, 5, 2, False), (2, 2, 20, 25, 64, 9, 4, False), (1, 1, 17, 20, 20, 3, 0, False),
+    (4, 1, 40, 256, 256, 5, 2, False),
+]
+
+
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "B%d_M%d_N%d_%dx%d_r%d_p%d_dw%d" % c)
+def test_direct_layers_match_oracle_and_nest(case):
+    B, M, N, H, W, r, pad, depthwise = case
+    print(f"direct case {case}", flush=True)
+    _, x, w = make_case(B, M, N, H, W, r, pad, seed=sum(case), x_dist="normal",
+                        w_dist="fanin_normal", depthwise=depthwise)
+    xd, wd = dev(x), dev(w)
+    ref = (direct_depthwise_conv2d if depthwise else direct_conv2d)(x, w, pad)
+    with nwg.Plan(B, M, N, H, W, r, pad, tile=AUTO, depthwise=depthwise) as plan:
+        y = torch.full(plan.y_shape, float("nan"), device="cuda")
+        plan.set_timing(True)
+        plan.conv2d(xd, wd, y)
+        torch.cuda.synchronize()
+        assert plan.direct and plan.get_timing()[1] == [1, 0, 1, 0]          # one kernel
+        # sums of fp32 products in two steps: about 2e-7 of the output
+        assert_close(y.cpu().numpy(), ref, rel_tol=1e-6, abs_frac=2e-6, what=str(case))
+        tile = plan.info["tile"]
+    with nwg.Plan(B, M, N, H, W, r, pad, tile=tile, depthwise=depthwise) as nest:
+        z = torch.full(nest.y_shape, float("nan"), device="cuda")
+        nest.conv2d(xd, wd, z)
+        torch.cuda.synchronize()
+        assert_close(y.cpu().numpy(), z.cpu().numpy().astype(np.float64), rel_tol=2e-5,
+                     abs_frac=1e-4, what=f"{case} against the nest")
+
+
+def test_direct_plan_keeps_its_weights():
+    """The plan's copy of the weights is what a call reads: a tensor changed in
+    place is copied again (its version), and a split-precision plan runs the nest."""
+    B, M, N, H, W, r, pad = 1, 32, 64, 48, 48, 5, 2
+    _, x, w1 = make_case(B, M, N, H, W, r, pad, seed=1)
+    _, _, w2 = make_case(B, M, N, H, W, r, pad, seed=2)
+    xd, wd = dev(x), dev(w1)
+    with nwg.Plan(B, M, N, H, W, r, pad, tile=AUTO) as plan:
+        y = torch.empty(plan.y_shape, device="cuda")
+        plan.conv2d(xd, wd, y)
+        assert_close(y.cpu().numpy(), direct_conv2d(x, w1, pad), what="first weights")
+        wd.copy_(dev(w2))
+        plan.conv2d(xd, wd, y)
+        assert_close(y.cpu().numpy(), direct_conv2d(x, w2, pad), what="changed in place")
+        plan.set_timing(True)
+        plan.set_precision(nwg.NWG_PRECISION_BF16_SPLIT)
+        plan.conv2d(xd, wd, y)
+        assert plan.get_timing()[1] == [1, 1, 1, 1]
+        assert_close(y.cpu().numpy(), direct_conv2d(x, w2, pad), what="split")
+        plan.set_precision(nwg.NWG_PRECISION_FP32)
+        plan.conv2d(xd, wd, y)
+        assert plan.get_timing()[1] == [1, 0, 1, 0]
+        assert_close(y.cpu().numpy(), direct_conv2d(x, w2, pad), what="fp32 again")
