@@ -18,7 +18,6 @@ from __future__ import annotations
 import argparse
 import hashlib
 import json
-import math
 import os
 import sys
 import time
@@ -93,6 +92,27 @@ def stage_bytes_flops(info: dict):
             "output_transform": (Zc + y, 0.0)}
 
 
+def conv2d_bytes_flops(info: dict, direct: bool = False):
+    """stage_bytes_flops of what conv2d itself runs, where that differs from the
+    stage calls: the level-1 taps of the mixed nest (level-1 digit 3 dead: U holds
+    4 values per channel pair and live group, V its 9 live points), or one direct
+    kernel (x and the plain weights in, y out)."""
+    bf = dict(stage_bytes_flops(info))
+    B, M, N, T, r = info["B"], info["M"], info["N"], info["T"], info["r"]
+    x, y = 4 * B * M * info["H"] * info["W"], 4 * B * N * info["Ho"] * info["Wo"]
+    w = 4 * N * (1 if info.get("depthwise") else M) * r * r
+    if direct:
+        return {"kernel_transform": (2 * w, 0.0), "contraction": (x + w + y, info["direct_flop"])}
+    if (info.get("tile") == NWG_TILE_MIX and info["n"] >= 3 and info.get("level1_live") == 0x7
+            and info.get("live_np", 0) > 0 and M % 8 == 0):
+        live = info["live_groups"]
+        U, V, Z = 16 * live * M * N, 36 * live * M * T, 16 * live * N * T
+        bf["kernel_transform"] = (w + U, 0.0)
+        bf["input_transform"] = (x + V, 0.0)
+        bf["contraction"] = (U + V + Z, info["contract_flop"])
+    return bf
+
+
 def source_hash(files):
     h = hashlib.sha256()
     for f in files:
@@ -102,7 +122,7 @@ def source_hash(files):
 
 
 KERNEL_SOURCES = {"input_transform": ["input_xform.hip", "mixed.hip", "nwg_internal.h"],
-                  "contraction": ["contract_mfma.hip", "nwg_internal.h"],
+                  "contraction": ["contract_mfma.hip", "taps.hip", "nwg_internal.h"],
                   "output_transform": ["output_xform.hip", "mixed.hip", "nwg_internal.h"],
                   "kernel_transform": ["kernel_xform.hip", "mixed.hip", "nwg_internal.h"]}
 
@@ -308,24 +328,22 @@ def run_workload(torch, nwg, name: str, tile: str, precision: str, steps: int, w
     warm = [p.get_timing() for p in plans]
     kx_first_ms = sum(ms[0] for ms, _ in warm)
     # steady-state kernel transform: the first call above also pays the lazy
-    # load of the code objects; time 3 more calls per layer into a spare U
+    # load of the code objects; time 3 more calls per layer
     kx_ms = 0.0
-    for p, w, ms in zip(plans, wds, (m for m, _ in warm)):
-        try:
-            U2 = torch.empty(p.u_shape, dtype=torch.float32, device="cuda")
-            p.kernel_transform(w, U2, stream)
-            k0, k1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
-            k0.record(stream)
-            for _ in range(3):
-                p.kernel_transform(w, U2, stream)
-            k1.record(stream)
-            torch.cuda.synchronize()
-            kx_ms += k0.elapsed_time(k1) / 3
-            del U2
-        except nwg.NwgError:
-            kx_ms += ms[0]      # no stage call (depth 0, depthwise): first call
-    # its algorithmic bytes (w read, U written), summed over layers
-    kx_bytes = float(sum(stage_bytes_flops(p.info)["kernel_transform"][0] for p in plans))
+    for p, w in zip(plans, wds):
+        p.set_weights(w, stream)
+        k0, k1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        k0.record(stream)
+        for _ in range(3):
+            p.set_weights(w, stream)
+        k1.record(stream)
+        torch.cuda.synchronize()
+        kx_ms += k0.elapsed_time(k1) / 3
+    for p in plans:
+        p.get_timing()
+    # its algorithmic bytes (w read, the plan's own U written), summed over layers
+    kx_bytes = float(sum(conv2d_bytes_flops(p.info, p.direct)["kernel_transform"][0]
+                         for p in plans))
 
     # the timed steps run with the library's per-stage events off (recording
     # them puts work between the launches); a second pass of K steps with
@@ -371,11 +389,8 @@ def run_workload(torch, nwg, name: str, tile: str, precision: str, steps: int, w
     direct_flop = float(sum(L.direct_flop for L in wl.layers))
     # per-stage accounting summed over layers
     stages = {}
-    for p, L, (ms, cnt) in zip(plans, wl.layers, timing):
-        bf = stage_bytes_flops(p.info)
-        if p.direct:                         # one kernel: x and the plain weights in, y out
-            bf = {"contraction": (4 * (L.B * L.M * L.H * L.W + math.prod(L.w_shape) +
-                                       L.B * L.N * L.Ho * L.Wo), float(L.direct_flop))}
+    for p, (ms, cnt) in zip(plans, timing):
+        bf = conv2d_bytes_flops(p.info, p.direct)
         parts = p.info["pipeline_parts"]
         for si, sname in enumerate(STAGES):
             if sname == "kernel_transform" or cnt[si] == 0:

@@ -31,6 +31,7 @@
 //                      12 x 12 block held in a scratch buffer Z3, then a
 //                      second kernel applies level 4 to the 25 blocks.
 #include "nwg_internal.h"
+#include "taps.h"
 
 namespace nwg {
 namespace {
@@ -66,8 +67,37 @@ __device__ __forceinline__ unsigned branch_live(unsigned long long m0, unsigned 
 
 // How a transform stores its points: every quad of a live branch, the live
 // quads only (quad layout), or the live points of the live groups in the
-// planar layout (nwg_plan_info::mix_planar).
-enum { kStoreAll = 0, kStoreMasked = 1, kStorePlanar = 2 };
+// planar layout (nwg_plan_info::mix_planar); kStoreTaps: the kernel transform's
+// level-1 taps of the live groups, U [live group][2 k1r + k1c][M][Np] (taps.hip).
+enum { kStoreAll = 0, kStoreMasked = 1, kStorePlanar = 2, kStoreTaps = 3 };
+
+// The level-1 taps of a branch from its 9 x 9 sub-kernel S (level-1 digit 3
+// dead: no tap has level-1 digit 2): G of level 2 along both axes.  put(q2r,
+// q2c, 2 k1r + k1c, value).
+template <class Put>
+__device__ __forceinline__ void taps_xform(const float (&S)[9][9], Put&& put) {
+#pragma unroll
+  for (int q2r = 0; q2r < 4; ++q2r)
+#pragma unroll
+    for (int k1r = 0; k1r < 2; ++k1r) {
+      float rowv[9];
+#pragma unroll
+      for (int ic = 0; ic < 9; ++ic) {
+        float sacc = 0.0f;
+#pragma unroll
+        for (int k2 = 0; k2 < 3; ++k2)
+          if (g_coef(q2r, k2) != 0.0f) sacc += g_coef(q2r, k2) * S[3 * k2 + k1r][ic];
+        rowv[ic] = sacc;
+      }
+#pragma unroll
+      for (int k1c = 0; k1c < 2; ++k1c) {
+        float o[4];
+        g_one(rowv[k1c], rowv[3 + k1c], rowv[6 + k1c], o);
+#pragma unroll
+        for (int q2c = 0; q2c < 4; ++q2c) put(q2r, q2c, 2 * k1r + k1c, o[q2c]);
+      }
+    }
+}
 
 // Whether quad q2r * 16 + q2c * 4 + q1r of a branch with live-group mask
 // live is stored.
@@ -203,6 +233,22 @@ __global__ __launch_bounds__(512) void kernel_xform_mix(const float* __restrict_
     unsigned nr = 0, nc = 0;                  // live nibbles of the row / column prefixes
     int lbase = 0, np = 0, r0 = 0, c0 = 0;     // ranks of the first row / column prefix
     __amdgpu_buffer_rsrc_t pr = rs;
+    if constexpr (STORE == kStoreTaps) {
+      static_assert(NO == 1, "depth 4 takes kernel_xform_mix_sep");
+      const int lnp = __popcll(m0), Np = (N + 3) & ~3;
+      const size_t MNp = (size_t)M * Np;
+      const unsigned rn = prefix_nibble(m0, m1, q3r), cn = prefix_nibble(m0, m1, q3c);
+      const int rr0 = prefix_rank(m0, m1, 4 * q3r), cc0 = prefix_rank(m0, m1, 4 * q3c);
+      const auto tr = span_rsrc(reinterpret_cast<float4*>(U + (size_t)m * Np + n0),
+                                (unsigned)(((size_t)lnp * lnp * 4 - 1) * MNp + (Np - n0)) * 4u);
+      taps_xform(S, [&](int q2r, int q2c, int tap, float v) {
+        const bool on = (live >> (q2r * 4 + q2c)) & 1u;
+        const int ir = rr0 + __popc(rn & ((1u << q2r) - 1u));
+        const int ic = cc0 + __popc(cn & ((1u << q2c) - 1u));
+        drop_store1(tr, on ? (unsigned)(((size_t)(ir * lnp + ic) * 4 + tap) * MNp + cl) * 4u : kDrop, v);
+      });
+      continue;
+    }
     if constexpr (STORE == kStorePlanar) {
       np = __popcll(m0) + __popcll(m1);
       int smin = 1 << 20;
@@ -272,7 +318,8 @@ __global__ __launch_bounds__(512) void kernel_xform_mix(const float* __restrict_
 // branch.  NW output channels per work-group (32 when their r x r kernels
 // fit in LDS, r <= 31): a wavefront's lanes store U in NW-float runs.
 // U [live group][3 q1r + q1c][M][N].
-template <int NW>
+// TAPS: U [live group][2 k1r + k1c][M][Np], the level-1 taps.
+template <int NW, bool TAPS>
 __global__ __launch_bounds__(NW * 32) void kernel_xform_mix_sep(const float* __restrict__ w,
                                                                 float* __restrict__ U, int M,
                                                                 int N, int r,
@@ -293,7 +340,9 @@ __global__ __launch_bounds__(NW * 32) void kernel_xform_mix_sep(const float* __r
   }
   __syncthreads();
   const int np = __popcll(m0) + __popcll(m1);
-  const size_t MN = (size_t)M * N;
+  const int ldn = TAPS ? (N + 3) & ~3 : N;
+  constexpr int PL = TAPS ? 4 : 9;           // planes of a group
+  const size_t MN = (size_t)M * ldn;
   const unsigned ps = (unsigned)MN * 4u;
 #pragma unroll 1
   for (int bc = 0; bc < 25; ++bc) {          // column branch: 5 q4c + q3c
@@ -368,8 +417,18 @@ __global__ __launch_bounds__(NW * 32) void kernel_xform_mix_sep(const float* __r
       const int r0 = prefix_rank(m0, m1, (q4r * 5 + q3r) * 4);
       const int c0 = prefix_rank(m0, m1, (q4c * 5 + q3c) * 4);
       const auto pr = span_rsrc(
-          reinterpret_cast<float4*>(U + (size_t)lbase * 9 * MN + (size_t)m * N + n0),
-          (unsigned)(20 * np * 9 * MN * 4));
+          reinterpret_cast<float4*>(U + (size_t)lbase * PL * MN + (size_t)m * ldn + n0),
+          (unsigned)(20 * np * PL * MN * 4));
+      if constexpr (TAPS) {
+        taps_xform(S, [&](int q2r, int q2c, int tap, float v) {
+          const bool on = (live >> (q2r * 4 + q2c)) & 1u;
+          const int ir = r0 + __popc(nr & ((1u << q2r) - 1u));
+          const int ic = c0 + __popc(nc & ((1u << q2c) - 1u));
+          const unsigned rel = (unsigned)((ir * np + ic - lbase) * 4 + tap);
+          drop_store1(pr, on ? (unsigned)(rel * MN + cln) * 4u : kDrop, v);
+        });
+        continue;
+      }
 #pragma unroll
       for (int rho = 0; rho < 16; ++rho) {
         const int q2r = rho >> 2, q1r = rho & 3;
@@ -501,7 +560,7 @@ template <int NO, int STORE, bool Q3, int TPW, int ROW>
 __device__ __forceinline__ void mix_branch(const float* win, int slot, int q4, int m, int t0,
                                            int tl, float4* __restrict__ V, int M, int T,
                                            long long qstride, unsigned long long m0,
-                                           unsigned long long m1, int q3) {
+                                           unsigned long long m1, int q3, int ldt) {
   const int t = t0 + tl;
   // a row of B^T of F(3,3) has its nonzero taps among 4 consecutive ones,
   // from tap 0 for row 0 and from tap 1 otherwise
@@ -569,17 +628,18 @@ __device__ __forceinline__ void mix_branch(const float* win, int slot, int q4, i
   }
   const int ob = q4 * 25 + slot;
   if constexpr (STORE == kStorePlanar) {
-    static_assert(NO == 2 && Q3, "planar V: depth 4, level-1 digit 3 dead");
+    static_assert(Q3, "planar V: level-1 digit 3 dead");
     // groups at their live-list places; the work-group's resource starts at
-    // its level-4 row block (q4r), 20 row prefixes
+    // its level-4 row block (q4r), 20 row prefixes (depth 3: the whole list);
+    // rows of ldt tiles
     const int np = __popcll(m0) + __popcll(m1);
     const int q4r = q4 / 5, q4c = q4 - 5 * q4r;
     const int lbase = prefix_rank(m0, m1, q4r * 20) * np;
-    const size_t plane = (size_t)M * T;
+    const size_t plane = (size_t)M * ldt;
     const auto pr = span_rsrc(reinterpret_cast<float4*>(reinterpret_cast<float*>(V) +
                                                         (size_t)lbase * 9 * plane +
-                                                        (size_t)m * T + t0),
-                              (unsigned)(20 * np * 9 * plane * 4));
+                                                        (size_t)m * ldt + t0),
+                              (unsigned)((NO == 2 ? 20 : np) * np * 9 * plane * 4));
     // ranks of the branch's first row and column prefixes; the other three
     // follow from the live nibbles
     const int br = q4r * 5 + q3r, bc = q4c * 5 + q3c;
@@ -621,12 +681,12 @@ __device__ __forceinline__ void mix_branch(const float* win, int slot, int q4, i
 // threads, one work-group per CU) write each point's V row in 512-byte runs:
 // 1.394 -> 1.372 ms on the 31 x 31 layer against 16 tiles.  Work-group ->
 // (level-4 branch q4 (NO = 2), TPW-tile chunk, channel m).
-// STORE = kStorePlanar: depth 4 and Q3 only, V [live group][3 q1r + q1c][M][T].
+// STORE = kStorePlanar: Q3 only, V [live group][3 q1r + q1c][M][ldt].
 template <int NO, int STORE, bool Q3>
 __global__ __launch_bounds__(NO == 2 ? 512 : 256) __attribute__((amdgpu_waves_per_eu(2))) void input_xform_mix(
     const float* __restrict__ x, const float* __restrict__ X4, float4* __restrict__ V, int M,
     int H, int W, int pad, int th, int tw, int T, long long qstride, unsigned long long m0,
-    unsigned long long m1, int q3) {
+    unsigned long long m1, int q3, int ldt) {
   constexpr int Mn = NO == 2 ? 36 : 12;
   constexpr int KK = kL3 * kL3;
   constexpr int TPW = NO == 2 ? 32 : 16, NT = 16 * TPW;   // tiles, threads per work-group
@@ -701,7 +761,8 @@ __global__ __launch_bounds__(NO == 2 ? 512 : 256) __attribute__((amdgpu_waves_pe
   if (t >= T) return;                       // no barrier below
   const float* win = lds + tl * kWS;
   for (int slot = threadIdx.x / TPW; slot < 25; slot += 16) {   // slot = 5 q3r + q3c
-    mix_branch<NO, STORE, Q3, TPW, kL3>(win, slot, q4, m, t0, tl, V, M, T, qstride, m0, m1, q3);
+    mix_branch<NO, STORE, Q3, TPW, kL3>(win, slot, q4, m, t0, tl, V, M, T, qstride, m0, m1, q3,
+                                         ldt);
   }
 }
 
@@ -743,7 +804,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void i
   const float* win = reinterpret_cast<const float*>(lds4) + lane * kPKB;
   for (int slot = wave; slot < 25; slot += 8)
     mix_branch<2, kStorePlanar, true, kPT, kPB>(win, slot, q4, m, t0, lane, V, M, T, 0, m0, m1,
-                                                1);
+                                                1, T);
 }
 
 // ---- output transform -------------------------------------------------------
@@ -942,7 +1003,7 @@ hipError_t launch_kernel_xform_mix(const nwg_plan_info& g, const float* w, float
     const bool wide = g.N % 32 == 0 && lds_of(32) <= 160 * 1024;
     const int nw = wide ? 32 : 16;
     const size_t ldsp = lds_of(nw);
-    const auto fk = wide ? &kernel_xform_mix_sep<32> : &kernel_xform_mix_sep<16>;
+    const auto fk = wide ? &kernel_xform_mix_sep<32, false> : &kernel_xform_mix_sep<16, false>;
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(fk),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)ldsp);
     if (e != hipSuccess) return e;
@@ -959,6 +1020,78 @@ hipError_t launch_kernel_xform_mix(const nwg_plan_info& g, const float* w, float
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(fn, grid, dim3(512), lds, s, w, U, g.M, g.N, g.r, g.live_prefix[0],
                      g.live_prefix[1], q3);
+  return hipGetLastError();
+}
+
+// Depth 4, level-1 digit 3 dead, T a multiple of 64: 25 x 25 level-4 blocks,
+// then 64 tiles per work-group, V [live group][9][M][T].
+static hipError_t input_planar64(const nwg_plan_info& g, const float* x, float4* V, float* X4,
+                                 hipStream_t s) {
+  if (mix_outer_levels(g) != 2 || g.level1_live != 0x7 || g.M > 65535 || g.T % kPT)
+    return hipErrorInvalidValue;
+  hipLaunchKernelGGL(input_mix_l4<kPB>, dim3((unsigned)g.T, (unsigned)g.M), dim3(256), 0, s, x, X4,
+                     g.M, g.H, g.W, g.pad, g.th, g.tw, (int)g.T);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  const size_t ldsp = (size_t)kPBlk * 64 * sizeof(float4);
+  e = hipFuncSetAttribute(reinterpret_cast<const void*>(&input_xform_mix_p64),
+                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)ldsp);
+  if (e != hipSuccess) return e;
+  const long long nwgp = (long long)(g.T / kPT) * g.M * 25;
+  if (nwgp > 0x7fffffffLL) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(input_xform_mix_p64, dim3((unsigned)nwgp), dim3(512), ldsp, s, X4, V, g.M,
+                     (int)g.T, g.live_prefix[0], g.live_prefix[1]);
+  return hipGetLastError();
+}
+
+// The plan's own layouts where nwg_conv2d runs on the level-1 taps (taps.hip).
+hipError_t launch_kernel_xform_taps(const nwg_plan_info& g, const float* w, float* U,
+                                    hipStream_t s) {
+  if (!taps_applies(g) || ((uintptr_t)U & 15)) return hipErrorInvalidValue;
+  if (mix_outer_levels(g) == 1) {
+    const size_t lds = (size_t)16 * 15 * 15 * sizeof(float);
+    kernel_xform_mix<1, kStoreTaps><<<dim3((unsigned)((g.N + 15) / 16), (unsigned)g.M), 512, lds, s>>>(
+        w, U, g.M, g.N, g.r, g.live_prefix[0], g.live_prefix[1], 1);
+    return hipGetLastError();
+  }
+  // 32 output channels per work-group when their kernels and C fit in LDS
+  const auto lds_of = [&](int nw) { return (size_t)nw * (g.r * g.r + 9 * g.r) * sizeof(float); };
+  const bool wide = g.N % 32 == 0 && lds_of(32) <= 160 * 1024;
+  const int nw = wide ? 32 : 16;
+  const auto fk = wide ? &kernel_xform_mix_sep<32, true> : &kernel_xform_mix_sep<16, true>;
+  const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(fk),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize,
+                                           (int)lds_of(nw));
+  if (e != hipSuccess) return e;
+  fk<<<dim3((unsigned)((g.N + nw - 1) / nw), (unsigned)g.M), nw * 32, lds_of(nw), s>>>(
+      w, U, g.M, g.N, g.r, g.live_prefix[0], g.live_prefix[1]);
+  return hipGetLastError();
+}
+
+hipError_t launch_input_xform_taps(const nwg_plan_info& g, const float* x, float* Vf, float* X4,
+                                   hipStream_t s) {
+  const int no = mix_outer_levels(g);
+  if (!taps_applies(g) || ((uintptr_t)Vf & 15) || (no == 2 && !X4)) return hipErrorInvalidValue;
+  float4* V = reinterpret_cast<float4*>(Vf);
+  if (no == 2 && g.T % kPT == 0) return input_planar64(g, x, V, X4, s);
+  const int tpw = no == 2 ? 32 : 16;
+  const long long nwg = (g.T + tpw - 1) / tpw * g.M * (no == 2 ? 25 : 1);
+  if (nwg > 0x7fffffffLL) return hipErrorInvalidValue;
+  const size_t lds = (size_t)tpw * kWS * sizeof(float);
+  const auto fn = no == 2 ? &input_xform_mix<2, kStorePlanar, true>
+                          : &input_xform_mix<1, kStorePlanar, true>;
+  if (no == 2) {
+    hipLaunchKernelGGL(input_mix_l4<kL3>, dim3((unsigned)g.T, (unsigned)g.M), dim3(256), 0, s, x,
+                       X4, g.M, g.H, g.W, g.pad, g.th, g.tw, (int)g.T);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    e = hipFuncSetAttribute(reinterpret_cast<const void*>(fn),
+                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+  }
+  fn<<<dim3((unsigned)nwg), no == 2 ? 512 : 256, lds, s>>>(
+      x, X4, V, g.M, g.H, g.W, g.pad, g.th, g.tw, (int)g.T, 0, g.live_prefix[0], g.live_prefix[1],
+      1, (int)((g.T + 3) & ~3LL));
   return hipGetLastError();
 }
 
@@ -984,23 +1117,7 @@ hipError_t launch_input_xform_mix(const nwg_plan_info& g, const float* x, float*
                     : (mask ? &input_xform_mix<2, K, false> : &input_xform_mix<2, A, false>))
               : (q3 ? (mask ? &input_xform_mix<1, K, true> : &input_xform_mix<1, A, true>)
                     : (mask ? &input_xform_mix<1, K, false> : &input_xform_mix<1, A, false>));
-  if (g.mix_planar) {
-    // 25 x 25 level-4 blocks, then 64 tiles per work-group
-    if (no != 2 || !q3 || g.M > 65535 || g.T % kPT) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(input_mix_l4<kPB>, dim3((unsigned)g.T, (unsigned)g.M), dim3(256), 0, s, x,
-                       X4, g.M, g.H, g.W, g.pad, g.th, g.tw, (int)g.T);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    const size_t ldsp = (size_t)kPBlk * 64 * sizeof(float4);
-    e = hipFuncSetAttribute(reinterpret_cast<const void*>(&input_xform_mix_p64),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)ldsp);
-    if (e != hipSuccess) return e;
-    const long long nwgp = (long long)(g.T / kPT) * g.M * 25;
-    if (nwgp > 0x7fffffffLL) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(input_xform_mix_p64, dim3((unsigned)nwgp), dim3(512), ldsp, s, X4, V, g.M,
-                       (int)g.T, g.live_prefix[0], g.live_prefix[1]);
-    return hipGetLastError();
-  }
+  if (g.mix_planar) return input_planar64(g, x, V, X4, s);
   if (no == 2) {
     if (g.M > 65535) return hipErrorInvalidValue;
     hipLaunchKernelGGL(input_mix_l4<kL3>, dim3((unsigned)g.T, (unsigned)g.M), dim3(256), 0, s, x,
@@ -1013,7 +1130,7 @@ hipError_t launch_input_xform_mix(const nwg_plan_info& g, const float* x, float*
   }
   hipLaunchKernelGGL(fn, dim3((unsigned)nwg), dim3(no == 2 ? 512 : 256), lds, s, x, X4, V, g.M,
                      g.H, g.W, g.pad, g.th, g.tw, (int)g.T, qstride, g.live_prefix[0],
-                     g.live_prefix[1], q3);
+                     g.live_prefix[1], q3, (int)g.T);
   return hipGetLastError();
 }
 

@@ -14,6 +14,7 @@
 
 #include "direct.h"
 #include "nwg_internal.h"
+#include "taps.h"
 
 namespace {
 
@@ -252,6 +253,13 @@ int run_pipelined(nwg_plan* p, const float* x, hipStream_t s) {
   return rc != NWG_OK ? rc : rw;
 }
 
+// The kernel transform into a plan's own U (mixed plans on the level-1 taps hold
+// those; the stage call writes the layouts of nwg.h).
+hipError_t own_kxform(const nwg_plan_info& g, const float* w, float* U, hipStream_t s) {
+  return nwg::taps_applies(g) ? nwg::launch_kernel_xform_taps(g, w, U, s)
+                              : launch_kxform(g, w, U, s);
+}
+
 // Whether nwg_conv2d runs the plan's layer direct: not in the precision or the
 // pipeline that only the nest has.
 bool runs_direct(const nwg_plan* p) {
@@ -264,7 +272,7 @@ bool runs_direct(const nwg_plan* p) {
 int run_kernel_transform(nwg_plan* p, const float* w, hipStream_t s) {
   return timed(p, 0, s, "kernel transform launch", [&] {
     return runs_direct(p) ? nwg::launch_direct_weights(p->info, w, p->U, s)
-                          : launch_kxform(p->info, w, p->U, s);
+                          : own_kxform(p->info, w, p->U, s);
   });
 }
 
@@ -314,6 +322,13 @@ int run_steps(nwg_plan* p, const nwg_plan_info& g, const Workspace& ws, const fl
   } else if (g.pipeline_parts > 1) {
     if (!p) return fail(NWG_EUNSUPPORTED, "the two-stream pipeline needs a plan");
     rc = run_pipelined(p, x, s);
+  } else if (nwg::taps_applies(g)) {
+    rc = timed(p, 1, s, "input transform launch", [&] {
+      return nwg::launch_input_xform_taps(g, x, ws.V, mix_scratch_of(g, ws.Yh), s);
+    });
+    if (rc != NWG_OK) return rc;
+    rc = timed(p, 2, s, "contraction launch",
+               [&] { return nwg::launch_contract_taps(g, U, ws.V, ws.Yh, s); });
   } else {
     rc = timed(p, 1, s, "input transform launch",
                [&] { return launch_ixform(g, x, ws.V, mix_scratch_of(g, ws.Yh), s); });
@@ -379,7 +394,7 @@ nwg_plan* create_plan(const nwg_plan_info& g, int tile) {
 namespace nwg {
 
 int kernel_transform_into(const nwg_plan_info& g, const float* w, float* U, hipStream_t s) {
-  return check_launch(launch_kxform(g, w, U, s), "kernel transform launch", s);
+  return check_launch(own_kxform(g, w, U, s), "kernel transform launch", s);
 }
 
 int direct_conv(const nwg_plan_info& g, const DirectShape& d, const float* x, const float* w,

@@ -549,6 +549,19 @@ int check_plan_request(const nwg_plan_info& g) {
   return NWG_OK;
 }
 
+bool taps_applies(const nwg_plan_info& g) {
+  if (g.tile != NWG_TILE_MIX_F23_F33 || g.n < 3 || g.level1_live != 0x7 || g.live_np <= 0)
+    return false;
+  if (g.M % 8 || g.M > 65535) return false;
+  const double Np = 4.0 * ((g.N + 3) / 4), Tp = 4.0 * ((g.T + 3) / 4), live = (double)g.live_groups;
+  const double u = 16.0 * live * g.M * Np, v = 36.0 * live * g.M * Tp;
+  if (u > (double)g.u_bytes || v > (double)g.v_bytes) return false;
+  // the transforms' stores: a level-4 row block (20 row prefixes; the whole
+  // list at depth 3) through one buffer resource
+  const double rows = g.n == 4 ? 20.0 : g.live_np;
+  return rows * g.live_np * 9.0 * g.M * (Np > Tp ? Np : Tp) * 4.0 < 2147483648.0;
+}
+
 // ---- direct kernels ----------------------------------------------------------
 
 int direct_toeplitz_row(int r, int wc) {

@@ -78,6 +78,12 @@ struct GroupMap {
 };
 GroupMap group_map(const nwg_plan_info& g);
 
+// Mixed-nest plans whose nwg_conv2d runs on the level-1 taps (taps.hip): level-1
+// digit 3 dead, a live list, whole chunks of 8 channels, and the layouts within
+// the plan's U and V and the transforms' 32-bit offsets.  The stage calls keep
+// the layouts of nwg.h.
+bool taps_applies(const nwg_plan_info& g);
+
 // Launch shape of a direct kernel (direct.hip), kDirectNone where the nest is
 // the faster one.
 enum DirectKind { kDirectNone = 0, kDirectToeplitz, kDirectValu, kDirectMfma };
