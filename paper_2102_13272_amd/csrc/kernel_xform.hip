@@ -16,6 +16,8 @@
 // consecutive output channels, then input channels, so the writes are
 // contiguous.  Depth 0 (r = 1) stores U[m][n] = w[n][m][0][0].
 #include "nwg_internal.h"
+#include "taps.h"
+#include "taps_device.h"
 
 namespace nwg {
 namespace {
@@ -164,10 +166,14 @@ __global__ __launch_bounds__(256) void kernel_xform(const float* __restrict__ w,
 // inner digits, run the two inner levels in registers and store 64 quads;
 // the 16 channels of a quarter-wave store 256 contiguous bytes per quad.
 // Every tap index is a compile-time constant.
-template <int NLEV, int NW>
+// TAPS: the live groups' level-1 taps, U [live group][2 k1r + k1c][M][Np]
+// (taps.hip; Np = N rounded up to 4, np live prefixes of mask m0): a quarter of
+// the bytes, which bound it from 48 x 80 channels on (r = 25, 128 -> 128 channels:
+// 909 -> 257 us).
+template <int NLEV, int NW, bool TAPS>
 __global__ __launch_bounds__(NW * 64) void kernel_xform_sep(const float* __restrict__ w,
                                                         float* __restrict__ U, int M, int N,
-                                                        int r) {
+                                                        int r, unsigned long long m0, int np) {
   constexpr int K = (2 << NLEV) - 1;        // padded taps per axis
   constexpr int KS = K * K;                 // LDS stride per channel (odd)
   constexpr int RS = 9 * K;                 // Rw stride per (branch, channel) (odd)
@@ -246,7 +252,21 @@ __global__ __launch_bounds__(NW * 64) void kernel_xform_sep(const float* __restr
             for (int ir = 0; ir < 9; ++ir) S[ir][ic] = fmaf(cf, rwl[ir * K + tap], S[ir][ic]);
           }
         }
-      if (nn < N) {
+      if constexpr (TAPS) {
+        // the wave's row branches share the level-4 row digit: one resource over
+        // its 16 row prefixes (depth 3: the whole list)
+        const int Np = (N + 3) & ~3;
+        const size_t MNp = (size_t)M * Np;
+        const BranchPlace pl(m0, 0, np, NLEV == 4 ? 4 * qr4 + qr3 : qr3, NLEV == 4 ? 4 * qc4 + qc3 : qc3);
+        const int first = NLEV == 4 ? prefix_rank(m0, 0, 16 * (rb0 >> 2)) * np : 0;
+        const auto tr = span_rsrc(
+            reinterpret_cast<float4*>(U + (size_t)first * 4 * MNp + (size_t)m * Np + n0),
+            (unsigned)((NLEV == 4 ? 16 : np) * np * 4 * MNp * 4));
+        taps_xform(S, [&](int q2r, int q2c, int tap, float v) {
+          const unsigned rel = (unsigned)((pl.at(q2r, q2c) - first) * 4 + tap);
+          drop_store1(tr, nn < N && pl.on(q2r, q2c) ? (unsigned)(rel * MNp + cl) * 4u : kDrop, v);
+        });
+      } else if (nn < N) {
         const int branch = NLEV == 4 ? ((qr4 * 4 + qc4) * 4 + qr3) * 4 + qc3 : qr3 * 4 + qc3;
         float4* ub = reinterpret_cast<float4*>(U) + (size_t)branch * 64 * MN + (size_t)m * N + nn;
 #pragma unroll
@@ -285,14 +305,16 @@ hipError_t launch_kernel_xform(const nwg_plan_info& g, const float* w, float* U,
     const int K = (2 << g.n) - 1;
     const size_t lds = ((size_t)16 * K * K + (size_t)64 * 9 * K) * sizeof(float);
     dim3 grid((unsigned)((g.N + 15) / 16), (unsigned)g.M);
-    const void* fn = g.n == 3 ? reinterpret_cast<const void*>(&kernel_xform_sep<3, 4>)
-                              : reinterpret_cast<const void*>(&kernel_xform_sep<4, 8>);
+    const void* fn = g.n == 3 ? reinterpret_cast<const void*>(&kernel_xform_sep<3, 4, false>)
+                              : reinterpret_cast<const void*>(&kernel_xform_sep<4, 8, false>);
     hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     if (g.n == 3)
-      hipLaunchKernelGGL((kernel_xform_sep<3, 4>), grid, dim3(256), lds, s, w, U, g.M, g.N, g.r);
+      hipLaunchKernelGGL((kernel_xform_sep<3, 4, false>), grid, dim3(256), lds, s, w, U, g.M, g.N,
+                         g.r, 0ull, 0);
     else
-      hipLaunchKernelGGL((kernel_xform_sep<4, 8>), grid, dim3(512), lds, s, w, U, g.M, g.N, g.r);
+      hipLaunchKernelGGL((kernel_xform_sep<4, 8, false>), grid, dim3(512), lds, s, w, U, g.M, g.N,
+                         g.r, 0ull, 0);
     return hipGetLastError();
   }
   const long long nthreads = (long long)g.N * g.M;
@@ -303,6 +325,51 @@ hipError_t launch_kernel_xform(const nwg_plan_info& g, const float* w, float* U,
     case 2: hipLaunchKernelGGL(kernel_xform<2>, grid, dim3(256), 0, s, w, U, g.M, g.N, g.r, nthreads); break;
     default: return hipErrorInvalidValue;
   }
+  return hipGetLastError();
+}
+
+// Depth 2 on the level-1 taps: one thread per (output channel n, input channel
+// m), U [16 groups][2 k1r + k1c][M][Np].
+__global__ __launch_bounds__(256) void kernel_xform_taps2(const float* __restrict__ w,
+                                                          float* __restrict__ U, int M, int N,
+                                                          int r, long long nthreads) {
+  const long long id = (long long)blockIdx.x * 256 + threadIdx.x;
+  if (id >= nthreads) return;
+  const int nn = (int)(id % N), m = (int)(id / N);
+  const int Np = (N + 3) & ~3;
+  const float* __restrict__ wk = w + ((size_t)nn * M + m) * r * r;
+  float S[9][9];                            // (k2, k1) of each axis
+#pragma unroll
+  for (int ir = 0; ir < 9; ++ir)
+#pragma unroll
+    for (int ic = 0; ic < 9; ++ic) {
+      const int tr = canonical_tap<2>(0, 0, ir / 3, ir % 3), tc = canonical_tap<2>(0, 0, ic / 3, ic % 3);
+      S[ir][ic] = tr >= 0 && tc >= 0 && tr < r && tc < r ? wk[tr * r + tc] : 0.0f;
+    }
+  taps_xform(S, [&](int q2r, int q2c, int tap, float v) {
+    U[((size_t)((4 * q2r + q2c) * 4 + tap) * M + m) * Np + nn] = v;
+  });
+}
+
+hipError_t launch_kernel_xform_taps_f23(const nwg_plan_info& g, const float* w, float* U,
+                                        hipStream_t s) {
+  if (!taps_applies(g) || g.tile != NWG_TILE_F2X2_3X3 || ((uintptr_t)U & 15))
+    return hipErrorInvalidValue;
+  if (g.n == 2) {
+    const long long nthreads = (long long)g.N * g.M;
+    kernel_xform_taps2<<<(unsigned)((nthreads + 255) / 256), 256, 0, s>>>(w, U, g.M, g.N, g.r,
+                                                                          nthreads);
+    return hipGetLastError();
+  }
+  const GroupMap gm = taps_groups(g);
+  const int K = (2 << g.n) - 1;
+  const size_t lds = ((size_t)16 * K * K + (size_t)64 * 9 * K) * sizeof(float);
+  const dim3 grid((unsigned)((g.N + 15) / 16), (unsigned)g.M);
+  const auto fn = g.n == 3 ? &kernel_xform_sep<3, 4, true> : &kernel_xform_sep<4, 8, true>;
+  const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(fn),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  if (e != hipSuccess) return e;
+  fn<<<grid, g.n == 3 ? 256 : 512, lds, s>>>(w, U, g.M, g.N, g.r, gm.mask0, gm.np);
   return hipGetLastError();
 }
 

@@ -32,26 +32,12 @@
 //                      second kernel applies level 4 to the 25 blocks.
 #include "nwg_internal.h"
 #include "taps.h"
+#include "taps_device.h"
 
 namespace nwg {
 namespace {
 
 constexpr int kStride3 = 4, kStride4 = 12;
-
-// Rank of axis prefix i among the live prefixes (the live ones below it),
-// branch-free over the four 32-bit words (a 64-bit shift by a lane-varying
-// amount became control flow that stopped the transforms' unrolling).
-__device__ __forceinline__ int prefix_rank(unsigned long long m0, unsigned long long m1, int i) {
-  const unsigned wd[4] = {(unsigned)m0, (unsigned)(m0 >> 32), (unsigned)m1, (unsigned)(m1 >> 32)};
-  int r = 0;
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int k = i - 32 * q;
-    const unsigned below = k <= 0 ? 0u : (k >= 32 ? 0xffffffffu : (1u << k) - 1u);
-    r += __popc(wd[q] & below);
-  }
-  return r;
-}
 
 // The live groups (q2r, q2c) of outer branch (q4r, q4c, q3r, q3c) as a
 // 16-bit mask, bit 4 q2r + q2c (NO = 1: no level-4 digits).  A group is live
@@ -70,34 +56,6 @@ __device__ __forceinline__ unsigned branch_live(unsigned long long m0, unsigned 
 // planar layout (nwg_plan_info::mix_planar); kStoreTaps: the kernel transform's
 // level-1 taps of the live groups, U [live group][2 k1r + k1c][M][Np] (taps.hip).
 enum { kStoreAll = 0, kStoreMasked = 1, kStorePlanar = 2, kStoreTaps = 3 };
-
-// The level-1 taps of a branch from its 9 x 9 sub-kernel S (level-1 digit 3
-// dead: no tap has level-1 digit 2): G of level 2 along both axes.  put(q2r,
-// q2c, 2 k1r + k1c, value).
-template <class Put>
-__device__ __forceinline__ void taps_xform(const float (&S)[9][9], Put&& put) {
-#pragma unroll
-  for (int q2r = 0; q2r < 4; ++q2r)
-#pragma unroll
-    for (int k1r = 0; k1r < 2; ++k1r) {
-      float rowv[9];
-#pragma unroll
-      for (int ic = 0; ic < 9; ++ic) {
-        float sacc = 0.0f;
-#pragma unroll
-        for (int k2 = 0; k2 < 3; ++k2)
-          if (g_coef(q2r, k2) != 0.0f) sacc += g_coef(q2r, k2) * S[3 * k2 + k1r][ic];
-        rowv[ic] = sacc;
-      }
-#pragma unroll
-      for (int k1c = 0; k1c < 2; ++k1c) {
-        float o[4];
-        g_one(rowv[k1c], rowv[3 + k1c], rowv[6 + k1c], o);
-#pragma unroll
-        for (int q2c = 0; q2c < 4; ++q2c) put(q2r, q2c, 2 * k1r + k1c, o[q2c]);
-      }
-    }
-}
 
 // Whether quad q2r * 16 + q2c * 4 + q1r of a branch with live-group mask
 // live is stored.
@@ -1045,8 +1003,8 @@ static hipError_t input_planar64(const nwg_plan_info& g, const float* x, float4*
 }
 
 // The plan's own layouts where nwg_conv2d runs on the level-1 taps (taps.hip).
-hipError_t launch_kernel_xform_taps(const nwg_plan_info& g, const float* w, float* U,
-                                    hipStream_t s) {
+hipError_t launch_kernel_xform_taps_mix(const nwg_plan_info& g, const float* w, float* U,
+                                        hipStream_t s) {
   if (!taps_applies(g) || ((uintptr_t)U & 15)) return hipErrorInvalidValue;
   if (mix_outer_levels(g) == 1) {
     const size_t lds = (size_t)16 * 15 * 15 * sizeof(float);
@@ -1068,8 +1026,8 @@ hipError_t launch_kernel_xform_taps(const nwg_plan_info& g, const float* w, floa
   return hipGetLastError();
 }
 
-hipError_t launch_input_xform_taps(const nwg_plan_info& g, const float* x, float* Vf, float* X4,
-                                   hipStream_t s) {
+hipError_t launch_input_xform_taps_mix(const nwg_plan_info& g, const float* x, float* Vf, float* X4,
+                                       hipStream_t s) {
   const int no = mix_outer_levels(g);
   if (!taps_applies(g) || ((uintptr_t)Vf & 15) || (no == 2 && !X4)) return hipErrorInvalidValue;
   float4* V = reinterpret_cast<float4*>(Vf);

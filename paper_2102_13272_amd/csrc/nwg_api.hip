@@ -253,7 +253,7 @@ int run_pipelined(nwg_plan* p, const float* x, hipStream_t s) {
   return rc != NWG_OK ? rc : rw;
 }
 
-// The kernel transform into a plan's own U (mixed plans on the level-1 taps hold
+// The kernel transform into a plan's own U (plans on the level-1 taps hold
 // those; the stage call writes the layouts of nwg.h).
 hipError_t own_kxform(const nwg_plan_info& g, const float* w, float* U, hipStream_t s) {
   return nwg::taps_applies(g) ? nwg::launch_kernel_xform_taps(g, w, U, s)

@@ -549,17 +549,45 @@ int check_plan_request(const nwg_plan_info& g) {
   return NWG_OK;
 }
 
+GroupMap taps_groups(const nwg_plan_info& g) {
+  GroupMap m = group_map(g);
+  if (m.np > 0) return m;
+  // every group of an F(2,3) chain
+  m = GroupMap{};
+  m.nd = g.n - 1;
+  m.np = 1 << (2 * m.nd);
+  m.mask0 = m.np >= 64 ? ~0ULL : (1ULL << m.np) - 1;
+  for (int d = 0, w = 1; d < m.nd; ++d, w *= 16) {
+    m.rad[d] = 4;
+    m.wc[d] = w;
+    m.wr[d] = 4 * w;
+  }
+  m.q3 = 1;
+  return m;
+}
+
 bool taps_applies(const nwg_plan_info& g) {
-  if (g.tile != NWG_TILE_MIX_F23_F33 || g.n < 3 || g.level1_live != 0x7 || g.live_np <= 0)
-    return false;
+  const bool mix = g.tile == NWG_TILE_MIX_F23_F33;
+  if (mix) {
+    if (g.n < 3 || g.level1_live != 0x7 || g.live_np <= 0) return false;
+  } else {
+    // F(2,3): only tap K_n - 1 splits to level-1 digit 2
+    if (g.tile != NWG_TILE_F2X2_3X3 || g.depthwise || g.n < 2 || g.r >= g.Kn) return false;
+    if (g.fused_input || g.fused_conv || g.fused_output) return false;
+    if (g.precision != NWG_PRECISION_FP32) return false;
+    // the two-stream pipeline reads quads, and may be switched while U is set
+    if (pipeline_allowed(g)) return false;
+  }
   if (g.M % 8 || g.M > 65535) return false;
-  const double Np = 4.0 * ((g.N + 3) / 4), Tp = 4.0 * ((g.T + 3) / 4), live = (double)g.live_groups;
+  const GroupMap gm = taps_groups(g);
+  const double Np = 4.0 * ((g.N + 3) / 4), Tp = 4.0 * ((g.T + 3) / 4);
+  const double live = (double)gm.np * gm.np;
   const double u = 16.0 * live * g.M * Np, v = 36.0 * live * g.M * Tp;
   if (u > (double)g.u_bytes || v > (double)g.v_bytes) return false;
-  // the transforms' stores: a level-4 row block (20 row prefixes; the whole
-  // list at depth 3) through one buffer resource
-  const double rows = g.n == 4 ? 20.0 : g.live_np;
-  return rows * g.live_np * 9.0 * g.M * (Np > Tp ? Np : Tp) * 4.0 < 2147483648.0;
+  // the transforms' stores: a level-4 row block (20 or 16 row prefixes; the
+  // whole list at the smaller depths) through one buffer resource
+  const double rows = g.n == 4 ? (mix ? 20.0 : 16.0) : gm.np;
+  return rows * gm.np * 9.0 * g.M * (Np > Tp ? Np : Tp) * 4.0 < 2147483648.0;
 }
 
 // ---- direct kernels ----------------------------------------------------------
@@ -622,7 +650,24 @@ bool direct_fits(const nwg_plan_info& g, const DirectShape& d) {
 // 2.5 TB/s in the single kernels.  Fitted to
 // 350 layers of 1..240 channels and 2..15 taps on maps of 8..256 values a side
 // (most within a third).
+// Plans on the level-1 taps: 9 of 16 points of V and 4 values of U, some 5 TB/s
+// (the mixed nest at depth 4 waits more for its chain over the channels), and
+// 160 TFLOP/s where the contraction adds to that;
+// fitted to 2300 layers (8 in 10 within 15 %).
 double nest_us(const nwg_plan_info& g) {
+  if (taps_applies(g)) {
+    const GroupMap gm = taps_groups(g);
+    const double L = (double)gm.np * gm.np, MN = (double)g.M * g.N, MT = (double)g.M * g.T;
+    const double mb = 1e-6 * (16.0 * L * MN + 72.0 * L * MT +
+                              2.0 * L / (double)(g.P / 16) * (double)g.yhat_bytes +
+                              4.0 * g.B * ((double)g.M * g.H * g.W + (double)g.N * g.Ho * g.Wo));
+    const double mflop = 18e-6 * L * MN * (double)g.T;
+    if (g.tile == NWG_TILE_MIX_F23_F33)
+      return g.n == 3 ? 44.0 + 0.03 * g.M + 0.24 * mb + 0.005 * mflop : 76.0 + 1.4 * g.M + 0.19 * mb;
+    return g.n == 2   ? 11.0 + 0.06 * g.M + 0.21 * mb + 0.006 * mflop
+           : g.n == 3 ? 19.5 + 0.05 * g.M + 0.17 * mb + 0.007 * mflop
+                      : 92.0 + 0.3 * g.M + 0.21 * mb;
+  }
   const bool f33 = g.tile == NWG_TILE_F3X3_3X3;
   if (g.fused_input && !f33) {
     const double serial = (g.n == 3 ? 1.5 : 2.2) * g.M, all = (double)g.P * g.T * g.M / 2e6;
@@ -738,6 +783,8 @@ DirectShape direct_shape(const nwg_plan_info& g, DirectKind kind) {
 // 125).
 DirectShape direct_route(const nwg_plan_info& g) {
   if (g.n == 0 || g.tile == NWG_TILE_LD_F2X2_3X3) return DirectShape();
+  // the two-stream pipeline needs the nest's U, and may be switched while U is set
+  if (pipeline_allowed(g)) return DirectShape();
   if (g.depthwise) {
     if (g.r <= 7) return DirectShape();
     return direct_shape(g, g.r <= 11 ? kDirectValu : kDirectToeplitz);

@@ -78,11 +78,14 @@ struct GroupMap {
 };
 GroupMap group_map(const nwg_plan_info& g);
 
-// Mixed-nest plans whose nwg_conv2d runs on the level-1 taps (taps.hip): level-1
-// digit 3 dead, a live list, whole chunks of 8 channels, and the layouts within
-// the plan's U and V and the transforms' 32-bit offsets.  The stage calls keep
-// the layouts of nwg.h.
+// Plans whose nwg_conv2d runs on the level-1 taps (taps.hip): the mixed nest, and
+// unfused dense fp32 F(2,3) chains at depth 2-4, where no tap k < r has level-1
+// digit 2 (r below the nest's taps) and that cannot be pipelined, with whole chunks
+// of 8 channels, and with the layouts within the plan's U and V and the transforms' 32-bit offsets.  The
+// stage calls keep the layouts of nwg.h.
 bool taps_applies(const nwg_plan_info& g);
+// The list of groups those plans compute (group_map, or every group).
+GroupMap taps_groups(const nwg_plan_info& g);
 
 // Launch shape of a direct kernel (direct.hip), kDirectNone where the nest is
 // the faster one.

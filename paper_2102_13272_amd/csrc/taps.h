@@ -1,4 +1,4 @@
-// The mixed nest's contraction from level-1 taps (taps.hip).
+// The contraction from level-1 taps (taps.hip) and the transforms it reads.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -11,10 +11,25 @@ namespace nwg {
 // (taps_applies plans)
 hipError_t launch_contract_taps(const nwg_plan_info& g, const float* U, const float* V, float* Z,
                                 hipStream_t s);
-// w -> U and x -> V in those layouts (mixed.hip)
-hipError_t launch_kernel_xform_taps(const nwg_plan_info& g, const float* w, float* U,
-                                    hipStream_t s);
-hipError_t launch_input_xform_taps(const nwg_plan_info& g, const float* x, float* V, float* X4,
-                                   hipStream_t s);
+// w -> U and x -> V in those layouts, on the mixed nest (mixed.hip) and on F(2,3)
+// chains (kernel_xform.hip, taps_input.hip); X4: the mixed nest's scratch
+hipError_t launch_kernel_xform_taps_mix(const nwg_plan_info& g, const float* w, float* U,
+                                        hipStream_t s);
+hipError_t launch_input_xform_taps_mix(const nwg_plan_info& g, const float* x, float* V, float* X4,
+                                       hipStream_t s);
+hipError_t launch_kernel_xform_taps_f23(const nwg_plan_info& g, const float* w, float* U,
+                                        hipStream_t s);
+hipError_t launch_input_xform_taps_f23(const nwg_plan_info& g, const float* x, float* V,
+                                       hipStream_t s);
+inline hipError_t launch_kernel_xform_taps(const nwg_plan_info& g, const float* w, float* U,
+                                           hipStream_t s) {
+  return g.tile == NWG_TILE_MIX_F23_F33 ? launch_kernel_xform_taps_mix(g, w, U, s)
+                                        : launch_kernel_xform_taps_f23(g, w, U, s);
+}
+inline hipError_t launch_input_xform_taps(const nwg_plan_info& g, const float* x, float* V,
+                                          float* X4, hipStream_t s) {
+  return g.tile == NWG_TILE_MIX_F23_F33 ? launch_input_xform_taps_mix(g, x, V, X4, s)
+                                        : launch_input_xform_taps_f23(g, x, V, s);
+}
 
 }  // namespace nwg

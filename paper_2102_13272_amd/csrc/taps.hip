@@ -1,6 +1,6 @@
-// The mixed nest's channel contraction where level-1 digit 3 is dead (r below
-// the nest's taps): no real tap then has level-1 digit 2, so the 9 live points
-// of a group come from 2 x 2 taps per (input, output) channel pair,
+// The channel contraction of the mixed nest and of F(2,3) chains where level-1
+// digit 3 is dead (r below the nest's taps): no real tap then has level-1 digit
+// 2, so the 9 live points of a group come from 2 x 2 taps per (input, output) channel pair,
 //
 //   G w: q = 0: w0,  q = 1: (w0 + w1) / 2,  q = 2: (w0 - w1) / 2   on each axis.
 //
@@ -323,7 +323,8 @@ template <int BM, int BN, int WM, int WN>
 hipError_t launch(const nwg_plan_info& g, const float* U, const float* V, float* Z, hipStream_t s) {
   const int T = (int)g.T, Np = (g.N + 3) & ~3, Tp = (T + 3) & ~3;
   const int ntb = (T + BN - 1) / BN, nnb = (g.N + BM - 1) / BM;
-  if ((double)ntb * nnb * (double)g.live_groups >= 2147483648.0) return hipErrorInvalidValue;
+  const GroupMap gm = taps_groups(g);
+  if ((double)ntb * nnb * gm.np * gm.np >= 2147483648.0) return hipErrorInvalidValue;
   int dev = 0, cus = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return e;
@@ -334,7 +335,7 @@ hipError_t launch(const nwg_plan_info& g, const float* U, const float* V, float*
   if (occ <= 0 || cus < 8) return hipErrorInvalidValue;
   const int wpx = cus / 8 * occ;                       // work-groups per XCD
   k<<<8 * wpx, 64 * WM * WN, 0, s>>>(U, V, reinterpret_cast<float4*>(Z), g.M, g.N, T, Np, Tp, ntb,
-                                     nnb, (int)g.live_groups, wpx, group_map(g));
+                                     nnb, gm.np * gm.np, wpx, gm);
   return hipGetLastError();
 }
 

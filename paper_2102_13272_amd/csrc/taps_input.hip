@@ -1,0 +1,287 @@
+// Input transform of F(2,3) chains (depth 2-4) for the contraction from level-1
+// taps (taps.hip): x -> V [live group][3 q1r + q1c][M][Tp], the live groups' 9
+// live points (level-1 digit 3 dead) as plain planes, Tp = T rounded up to 4.
+//
+// Bound by its stores: 9/16 of the quad layout's points.  A point's tiles are
+// contiguous, so a wavefront takes 64 tiles (its lanes) of one branch and stores
+// 256-byte runs; with fewer than 48 tiles, or where 64 of them would leave CUs
+// idle (under 256 work-groups; depth 2, whose work-groups are smaller, under 512),
+// its lanes take 16 tiles of four branches.  2 images 56 x 59 of 8 channels, r = 12
+// (T = 112): 9.6 us so, 14 with 64 tiles, 12.0 as quads.  3 images 45 x 61 of 48
+// channels, r = 11 (T = 144): 13.8 us, quads 17.3.
+#include "nwg_internal.h"
+#include "taps.h"
+#include "taps_device.h"
+
+namespace nwg {
+namespace {
+
+// ---- depth 3 and 4 ----------------------------------------------------------
+// Work-group: TPW tiles of one channel (and at depth 4 one level-4 branch, q4
+// fastest, dealt per XCD as in the quad kernel): the tiles' 21 x 21 windows
+// (after the level-4 B^T rows at depth 4) in LDS, an odd stride apart; then a
+// level-3 branch (slot) of a tile per lane.  Row and column 21 of the window
+// feed the dead digit only.
+template <int NLEV, int TPW>
+__global__ __launch_bounds__(TPW == 64 ? 512 : 256) void input_taps_tiles(
+    const float* __restrict__ x, float* __restrict__ V, int M, int H, int W, int pad, int th,
+    int tw, int T, int Tp, unsigned long long m0, int np) {
+  constexpr int NT = TPW == 64 ? 512 : 256;
+  constexpr int Mn = 1 << NLEV;
+  constexpr int L3 = 21, WS = L3 * L3;       // 441, odd: consecutive tiles in different banks
+  constexpr int TPT = NT / TPW;              // threads of a tile's fill
+  extern __shared__ float lds[];
+  const long long lid = xcd_remap(blockIdx.x, gridDim.x);
+  const int q4 = NLEV == 4 ? (int)(lid % 16) : 0;
+  const long long rest = NLEV == 4 ? lid / 16 : lid;
+  const int nchunk = (T + TPW - 1) / TPW;
+  const int t0 = (int)(rest % nchunk) * TPW;
+  const int m = (int)(rest / nchunk);
+  const int q4r = q4 >> 2, q4c = q4 & 3;
+  if constexpr (NLEV == 4) {
+    // a level-4 branch whose 16 row or column prefixes are all dead
+    if (((m0 >> (16 * q4r)) & 0xffffu) == 0 || ((m0 >> (16 * q4c)) & 0xffffu) == 0) return;
+  }
+  const int tpi = th * tw;
+  {
+    // thread (tile ftl, fj) fills columns fj, fj + TPT, ...: unconditional
+    // clamped loads, masked afterwards, a batch of rows in flight
+    const int ftl = threadIdx.x / TPT, fj = threadIdx.x % TPT;
+    const int t = t0 + ftl;
+    if (t < T) {
+      const int b = t / tpi;
+      const int r2 = t - b * tpi;
+      const int ty = r2 / tw, tx = r2 - ty * tw;
+      const float* __restrict__ xp = x + ((size_t)b * M + m) * H * W;
+      const int gr0 = ty * Mn - pad, gc0 = tx * Mn - pad;
+      float* dst = lds + ftl * WS;
+      auto clampi = [](int v, int hi) { return v < 0 ? 0 : (v > hi ? hi : v); };
+      if constexpr (NLEV == 4) {
+        const int a4r0 = 8 * bt_tap0(q4r), a4r1 = 8 * bt_tap1(q4r);
+        const int a4c0 = 8 * bt_tap0(q4c), a4c1 = 8 * bt_tap1(q4c);
+        const float s4r0 = bt_sign0(q4r), s4r1 = bt_sign1(q4r);
+        const float s4c0 = bt_sign0(q4c), s4c1 = bt_sign1(q4c);
+        for (int c = fj; c < L3; c += TPT) {
+          const int ca = gc0 + c + a4c0, cb = gc0 + c + a4c1;
+          const float mca = (ca >= 0 && ca < W) ? s4c0 : 0.0f;
+          const float mcb = (cb >= 0 && cb < W) ? s4c1 : 0.0f;
+          const int cac = clampi(ca, W - 1), cbc = clampi(cb, W - 1);
+          constexpr int RB = 7;              // rows per batch: 28 loads in flight
+#pragma unroll 1
+          for (int r0 = 0; r0 < L3; r0 += RB) {
+            float va[RB], vb[RB], vc[RB], vd[RB];
+#pragma unroll
+            for (int k = 0; k < RB; ++k) {
+              const int rac = clampi(gr0 + r0 + k + a4r0, H - 1);
+              const int rbc = clampi(gr0 + r0 + k + a4r1, H - 1);
+              va[k] = xp[(size_t)rac * W + cac];
+              vb[k] = xp[(size_t)rac * W + cbc];
+              vc[k] = xp[(size_t)rbc * W + cac];
+              vd[k] = xp[(size_t)rbc * W + cbc];
+            }
+#pragma unroll
+            for (int k = 0; k < RB; ++k) {
+              const int ra = gr0 + r0 + k + a4r0, rb = gr0 + r0 + k + a4r1;
+              const float mra = (ra >= 0 && ra < H) ? s4r0 : 0.0f;
+              const float mrb = (rb >= 0 && rb < H) ? s4r1 : 0.0f;
+              dst[(r0 + k) * L3 + c] =
+                  mra * (mca * va[k] + mcb * vb[k]) + mrb * (mca * vc[k] + mcb * vd[k]);
+            }
+          }
+        }
+      } else {
+        for (int c = fj; c < L3; c += TPT) {
+          const int gc = gc0 + c;
+          const bool cok = gc >= 0 && gc < W;
+          const int gcc = clampi(gc, W - 1);
+          float va[L3];
+#pragma unroll
+          for (int row = 0; row < L3; ++row) va[row] = xp[(size_t)clampi(gr0 + row, H - 1) * W + gcc];
+#pragma unroll
+          for (int row = 0; row < L3; ++row) {
+            const int gr = gr0 + row;
+            dst[row * L3 + c] = cok && gr >= 0 && gr < H ? va[row] : 0.0f;
+          }
+        }
+      }
+    }
+  }
+  __syncthreads();
+  const int tl = threadIdx.x % TPW;
+  if (t0 + tl >= T) return;                  // no barrier below
+  const float* win = lds + tl * WS;
+  const size_t plane = (size_t)M * Tp;
+  // one resource over the level-4 row branch's 16 row prefixes (depth 3: the
+  // whole list)
+  const int first = NLEV == 4 ? prefix_rank(m0, 0, 16 * q4r) * np : 0;
+  const auto rs = span_rsrc(
+      reinterpret_cast<float4*>(V + (size_t)first * 9 * plane + (size_t)m * Tp + t0),
+      (unsigned)((NLEV == 4 ? 16 : np) * np * 9 * plane * 4));
+  const unsigned ps = (unsigned)plane * 4u;
+  int slot = threadIdx.x / TPW;
+  if constexpr (TPW == 64) slot = __builtin_amdgcn_readfirstlane(slot);
+#pragma unroll 1
+  for (; slot < 16; slot += TPT) {           // level-3 branch (q3r, q3c)
+    const int q3r = slot >> 2, q3c = slot & 3;
+    const BranchPlace pl(m0, 0, np, NLEV == 4 ? 4 * q4r + q3r : q3r,
+                         NLEV == 4 ? 4 * q4c + q3c : q3c);
+    if (pl.live == 0) continue;
+    // level 3 (stride 4): two row taps and two column taps
+    const int ro0 = 4 * bt_tap0(q3r), ro1 = 4 * bt_tap1(q3r);
+    const int co0 = 4 * bt_tap0(q3c), co1 = 4 * bt_tap1(q3c);
+    const float rs0 = bt_sign0(q3r), rs1 = bt_sign1(q3r);
+    const float cs0 = bt_sign0(q3c), cs1 = bt_sign1(q3c);
+    const float* w00 = win + ro0 * L3 + co0;
+    const float* w01 = win + ro0 * L3 + co1;
+    const float* w10 = win + ro1 * L3 + co0;
+    const float* w11 = win + ro1 * L3 + co1;
+    float S[10][10];
+#pragma unroll
+    for (int i = 0; i < 9; ++i)
+#pragma unroll
+      for (int j = 0; j < 9; ++j) {
+        const float a = cs0 * w00[i * L3 + j] + cs1 * w01[i * L3 + j];
+        const float c = cs0 * w10[i * L3 + j] + cs1 * w11[i * L3 + j];
+        S[i][j] = rs0 * a + rs1 * c;
+      }
+    inner2_xform<false, true>(S, [&](int quad, float4 v) {
+      const int q2r = quad >> 4, q2c = (quad >> 2) & 3, q1r = quad & 3;
+      const unsigned o = (unsigned)((pl.at(q2r, q2c) - first) * 9 + 3 * q1r) * ps + (unsigned)tl * 4u;
+      const unsigned off = pl.on(q2r, q2c) ? o : kDrop;
+      drop_store1(rs, off, v.x);
+      drop_store1(rs, off, v.y, ps);
+      drop_store1(rs, off, v.z, 2 * ps);
+    });
+  }
+}
+
+// ---- depth 2 ----------------------------------------------------------------
+// Work-group: RX x RY (at most TPW) tiles of one image and channel, their union
+// box in LDS; then a tile and one of its 12 live rows (q2r, q1r) per lane: both
+// steps of the rows from four rows of the tile, both steps of the columns in
+// registers.
+template <int TPW>
+__global__ __launch_bounds__(256) void input_taps_d2(const float* __restrict__ x,
+                                                     float* __restrict__ V, int M, int H, int W,
+                                                     int pad, int th, int tw, int Tp, int RX,
+                                                     int RY, int nbx, int nby, int BW,
+                                                     unsigned bw_magic, unsigned rx_magic) {
+  constexpr int Mn = 4, L = 9;               // the dead digit alone reads row and column 9
+  extern __shared__ float lds[];
+  const int m = blockIdx.y;
+  int bid = blockIdx.x;
+  const int bx = bid % nbx;
+  bid /= nbx;
+  const int by = bid % nby;
+  const int b = bid / nby;
+  const int ty0 = by * RY, tx0 = bx * RX;
+  const int BH = (RY - 1) * Mn + L, cols = (RX - 1) * Mn + L;
+  const int r0 = ty0 * Mn - pad, c0 = tx0 * Mn - pad;
+  const float* __restrict__ xp = x + ((size_t)b * M + m) * H * W;
+  constexpr int NB = TPW == 64 ? 4 : 2;      // loads in flight
+  for (int e0 = threadIdx.x; e0 < BH * BW; e0 += 256 * NB) {
+    float v[NB];
+#pragma unroll
+    for (int k = 0; k < NB; ++k) {
+      const int e = e0 + 256 * k;
+      const int row = (int)__umulhi((unsigned)e, bw_magic), col = e - row * BW;
+      const int gr = r0 + row, gc = c0 + col;
+      const int grc = gr < 0 ? 0 : (gr > H - 1 ? H - 1 : gr);
+      const int gcc = gc < 0 ? 0 : (gc > W - 1 ? W - 1 : gc);
+      const float u = xp[(size_t)grc * W + gcc];
+      v[k] = gr == grc && gc == gcc && col < cols ? u : 0.0f;
+    }
+#pragma unroll
+    for (int k = 0; k < NB; ++k)
+      if (e0 + 256 * k < BH * BW) lds[e0 + 256 * k] = v[k];
+  }
+  __syncthreads();
+  const int tl = threadIdx.x % TPW;
+  const int ly = RX == 1 ? tl : (int)__umulhi((unsigned)tl, rx_magic), lx = tl - ly * RX;
+  const int ty = ty0 + ly, tx = tx0 + lx;
+  if (ly >= RY || ty >= th || tx >= tw) return;
+  const float* win = lds + ly * Mn * BW + lx * Mn;
+  const size_t plane = (size_t)M * Tp;
+  float* vt = V + (size_t)m * Tp + (size_t)(b * th + ty) * tw + tx;
+  int rho = threadIdx.x / TPW;
+  if constexpr (TPW == 64) rho = __builtin_amdgcn_readfirstlane(rho);
+#pragma unroll 1
+  for (; rho < 12; rho += 256 / TPW) {
+    const int q2r = rho / 3, q1r = rho - 3 * q2r;
+    const float s2[2] = {bt_sign0(q2r), bt_sign1(q2r)}, s1[2] = {bt_sign0(q1r), bt_sign1(q1r)};
+    const int a2[2] = {2 * bt_tap0(q2r), 2 * bt_tap1(q2r)}, a1[2] = {bt_tap0(q1r), bt_tap1(q1r)};
+    float R[10], z[2][9];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {            // level 2's rows, at level-1 tap i
+      const float* p = win + (a2[0] + a1[i]) * BW;
+      const float* q = win + (a2[1] + a1[i]) * BW;
+#pragma unroll
+      for (int c = 0; c < 8; c += 4) {
+        const float4 f = *reinterpret_cast<const float4*>(p + c);
+        const float4 h = *reinterpret_cast<const float4*>(q + c);
+        z[i][c] = s2[0] * f.x + s2[1] * h.x;
+        z[i][c + 1] = s2[0] * f.y + s2[1] * h.y;
+        z[i][c + 2] = s2[0] * f.z + s2[1] * h.z;
+        z[i][c + 3] = s2[0] * f.w + s2[1] * h.w;
+      }
+      z[i][8] = s2[0] * p[8] + s2[1] * q[8];
+    }
+#pragma unroll
+    for (int j = 0; j < L; ++j) R[j] = s1[0] * z[0][j] + s1[1] * z[1][j];
+    float o[16];
+    bt_inner2<true>(R, o);                   // q2c * 4 + q1c
+    float* vb = vt + (size_t)(4 * q2r * 9 + 3 * q1r) * plane;
+#pragma unroll
+    for (int q2c = 0; q2c < 4; ++q2c)
+#pragma unroll
+      for (int q1c = 0; q1c < 3; ++q1c) vb[(size_t)(q2c * 9 + q1c) * plane] = o[q2c * 4 + q1c];
+  }
+}
+
+}  // namespace
+
+hipError_t launch_input_xform_taps_f23(const nwg_plan_info& g, const float* x, float* V,
+                                       hipStream_t s) {
+  if (!taps_applies(g) || g.tile != NWG_TILE_F2X2_3X3 || ((uintptr_t)V & 15))
+    return hipErrorInvalidValue;
+  const int T = (int)g.T, Tp = (T + 3) & ~3;
+  if (g.n == 2) {
+    const int RX = g.tw < 16 ? g.tw : 16;
+    auto rows = [&](int tpw) { return tpw / RX > g.th ? g.th : tpw / RX; };
+    const int nbx = (g.tw + RX - 1) / RX;
+    auto blocks = [&](int tpw) {
+      return (long long)nbx * ((g.th + rows(tpw) - 1) / rows(tpw)) * g.B;
+    };
+    const int tpw = blocks(64) * g.M >= 512 ? 64 : 16;
+    const int RY = rows(tpw), nby = (g.th + RY - 1) / RY;
+    const int BW = (RX - 1) * 4 + 12;        // rows of whole quads
+    const size_t lds = (size_t)((RY - 1) * 4 + 9) * BW * sizeof(float);
+    const long long nwg = blocks(tpw);
+    if (nwg > 0x7fffffffLL) return hipErrorInvalidValue;
+    // e / d as the high word of e * (2^32 / d rounded up): exact for e d < 2^32, d > 1
+    auto magic = [](int d) { return (unsigned)((0x100000000ULL + d - 1) / d); };
+    const auto fn = tpw == 64 ? &input_taps_d2<64> : &input_taps_d2<16>;
+    fn<<<dim3((unsigned)nwg, (unsigned)g.M), 256, lds, s>>>(x, V, g.M, g.H, g.W, g.pad, g.th, g.tw,
+                                                           Tp, RX, RY, nbx, nby, BW, magic(BW),
+                                                           magic(RX));
+    return hipGetLastError();
+  }
+  const GroupMap gm = taps_groups(g);
+  const long long per = (long long)g.M * (g.n == 4 ? 16 : 1);
+  const int tpw = T >= 48 && (long long)((T + 63) / 64) * per >= 256 ? 64 : 16;
+  const long long nwg = (long long)((T + tpw - 1) / tpw) * per;
+  if (nwg > 0x7fffffffLL) return hipErrorInvalidValue;
+  const size_t lds = (size_t)tpw * 21 * 21 * sizeof(float);
+  const auto fn = g.n == 3 ? (tpw == 64 ? &input_taps_tiles<3, 64> : &input_taps_tiles<3, 16>)
+                           : (tpw == 64 ? &input_taps_tiles<4, 64> : &input_taps_tiles<4, 16>);
+  if (lds > 64 * 1024) {
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(fn),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+  }
+  fn<<<(unsigned)nwg, tpw == 64 ? 512 : 256, lds, s>>>(x, V, g.M, g.H, g.W, g.pad, g.th, g.tw, T,
+                                                       Tp, gm.mask0, gm.np);
+  return hipGetLastError();
+}
+
+}  // namespace nwg

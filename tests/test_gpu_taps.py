@@ -73,3 +73,55 @@ def test_mixed_layers_on_taps_match_oracle(case):
         torch.cuda.synchronize()
         assert_close(got, z.cpu().numpy().astype(np.float64),
                      rel_tol=1e-5 if r <= 15 else 4e-5, what=f"{case} against the stage calls")
+
+
+F23 = nwg.NWG_TILE_F2X2_3X3
+
+# F(2,3) chains: (B, M, N, H, W, r, pad)
+F23_CASES = [
+    (1, 16, 4, 5, 5, 4, 0),           # depth 2: one tile
+    (1, 8, 17, 9, 70, 4, 1),          # even kernel, more than 16 tiles across
+    (2, 16, 8, 70, 6, 5, 1),          # one tile across
+    (8, 32, 8, 61, 70, 5, 2),         # 64 tiles a work-group
+    (2, 24, 33, 31, 22, 5, 2),
+    (3, 40, 70, 56, 50, 6, 2),        # the last r of depth 2 with digit 3 dead
+    (1, 8, 24, 12, 12, 8, 3),         # depth 3: T = 4
+    (1, 16, 36, 45, 61, 11, 5),       # T = 48
+    (3, 264, 40, 45, 40, 13, 6),      # T = 90: 64 tiles a work-group
+    (2, 136, 66, 20, 23, 14, 7),      # the last r of depth 3
+    (1, 8, 20, 30, 30, 16, 7),        # depth 4: T = 4
+    (1, 16, 36, 75, 40, 25, 12),      # T = 15
+    (3, 8, 33, 70, 60, 17, 8),        # T = 60: 64 tiles a work-group
+    (2, 24, 17, 101, 80, 30, 15),     # the last r of depth 4, T = 70
+    (1, 32, 64, 128, 128, 20, 9),     # can be pipelined: the quad layout
+    (1, 12, 20, 30, 30, 12, 6),       # M = 12: the quad layout
+    (1, 16, 20, 30, 30, 15, 7),       # r = 15: level-1 digit 3 live
+]
+
+
+@pytest.mark.parametrize("case", F23_CASES, ids=lambda c: "B%d_M%d_N%d_%dx%d_r%d_p%d" % c)
+def test_f23_layers_on_taps_match_oracle(case):
+    B, M, N, H, W, r, pad = case
+    print(f"F(2,3) taps case {case}", flush=True)
+    _, x, w = make_case(B, M, N, H, W, r, pad, seed=sum(case), x_dist="normal",
+                        w_dist="fanin_normal")
+    xd, wd = dev(x), dev(w)
+    ref = direct_conv2d(x, w, pad)
+    with nwg.Plan(B, M, N, H, W, r, pad, tile=F23) as plan:
+        y = torch.full(plan.y_shape, float("nan"), device="cuda")
+        for _ in range(2):
+            plan.conv2d(xd, wd, y)
+        torch.cuda.synchronize()
+        # F(2,3) nests: some 5e-7 of the output at every depth here
+        assert_close(y.cpu().numpy(), ref, rel_tol=1e-5, what=str(case))
+        U = torch.empty(plan.u_shape, device="cuda")
+        V = torch.empty(plan.v_shape, device="cuda")
+        Z = torch.empty(plan.z_shape, device="cuda")
+        z = torch.full(plan.y_shape, float("nan"), device="cuda")
+        plan.kernel_transform(wd, U)
+        plan.input_transform(xd, V)
+        plan.contract(U, V, Z)
+        plan.output_transform(Z, z)
+        torch.cuda.synchronize()
+        assert_close(y.cpu().numpy(), z.cpu().numpy().astype(np.float64), rel_tol=1e-5,
+                     what=f"{case} against the stage calls")
