@@ -87,13 +87,17 @@ __global__ __launch_bounds__(256) void kernel_xform5(const float* __restrict__ w
 template <int NLEV>
 __global__ __launch_bounds__(320) void input_xform5(const float* __restrict__ x,
                                                     float* __restrict__ V, int M, int H, int W,
-                                                    int pad, int th, int tw, int T, int RX, int RY,
-                                                    int nbx, int nby) {
+                                                    int pad, int th, int tw, int ld, int RX,
+                                                    int RY, int nbx, int nby,
+                                                    unsigned bw_magic) {
   constexpr int Mn = NLEV == 1 ? 3 : 9;
   constexpr int Ln = NLEV == 1 ? 5 : 17;
   extern __shared__ float box[];
-  const int m = blockIdx.y;
-  int bid = blockIdx.x;
+  // neighbouring boxes and images, which share lines of V, on one XCD
+  const long long lid = xcd_remap((long long)blockIdx.y * gridDim.x + blockIdx.x,
+                                  (long long)gridDim.x * gridDim.y);
+  const int m = (int)(lid / gridDim.x);
+  int bid = (int)(lid - (long long)m * gridDim.x);
   const int bx = bid % nbx;
   bid /= nbx;
   const int by = bid % nby;
@@ -112,7 +116,7 @@ __global__ __launch_bounds__(320) void input_xform5(const float* __restrict__ x,
 #pragma unroll
     for (int u = 0; u < FB; ++u) {
       const int e = e0 + u * nth;
-      const int row = e / BW, col = e - row * BW;
+      const int row = (int)__umulhi((unsigned)e, bw_magic), col = e - row * BW;   // e / BW
       const int gr = r0 + row, gc = c0 + col;
       v[u] = 0.0f;
       if (e < nbox && gr >= 0 && gr < H && gc >= 0 && gc < W) v[u] = xp[(size_t)gr * W + gc];
@@ -123,16 +127,16 @@ __global__ __launch_bounds__(320) void input_xform5(const float* __restrict__ x,
   }
   __syncthreads();
   const int s = threadIdx.x & 63;                      // tile within the box (<= 64)
-  const int q2r = NLEV == 1 ? 0 : (int)(threadIdx.x >> 6);
+  const int q2r = NLEV == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (NLEV == 1 && threadIdx.x >= 64) return;
   if (s >= RX * RY) return;
   const int ly = s / RX, lx = s - ly * RX;
   const int ty = ty0 + ly, tx = tx0 + lx;
   if (ty >= th || tx >= tw) return;
-  const int t = (b * th + ty) * tw + tx;
+  const unsigned t = (unsigned)((b * th + ty) * tw + tx);
   const float* win = box + ly * Mn * BW + lx * Mn;
-  const size_t pstride = (size_t)M * T;
-  float* __restrict__ vp = V + (size_t)m * T + t;
+  const size_t pstride = (size_t)M * ld;               // ld: T, or T rounded up to 4
+  float* __restrict__ vm = V + (size_t)m * ld;         // uniform: a plane's address is scalar
   if constexpr (NLEV == 1) {
     float X[5][5];
 #pragma unroll
@@ -153,7 +157,7 @@ __global__ __launch_bounds__(320) void input_xform5(const float* __restrict__ x,
       float o[5];
       bt5_vec(C[q1r], o);
 #pragma unroll
-      for (int q1c = 0; q1c < 5; ++q1c) vp[(size_t)(q1r * 5 + q1c) * pstride] = o[q1c];
+      for (int q1c = 0; q1c < 5; ++q1c) (vm + (size_t)(q1r * 5 + q1c) * pstride)[t] = o[q1c];
     }
   } else {
     // level 2 along the rows (stride 3) for this wavefront's digit q2r:
@@ -176,16 +180,24 @@ __global__ __launch_bounds__(320) void input_xform5(const float* __restrict__ x,
         for (int c = 0; c < 17; ++c) Rw[a1][c] = fmaf(c2v[a2], rowp[c], Rw[a1][c]);
       }
     }
-#pragma unroll
+    // a row digit per iteration, with the coefficients of its row of B^T selected:
+    // unrolled, the kernel took 163 registers, and a CU held one work-group at a
+    // time (128 channels, 784 tiles: 103 us, with the scalar plane addresses and the
+    // box's order over the XCDs 90-94; so 80-84, 3.1 TB/s)
+#pragma unroll 1
     for (int q1r = 0; q1r < 5; ++q1r) {
       // level 1 along the rows
+      float c1v[5] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+      for (int q = 0; q < 5; ++q)
+#pragma unroll
+        for (int a1 = 0; a1 < 5; ++a1) c1v[a1] = q1r == q ? bt5(q, a1) : c1v[a1];
       float R[17];
 #pragma unroll
       for (int c = 0; c < 17; ++c) {
-        float sr = 0.0f;
+        float sr = c1v[0] * Rw[0][c];
 #pragma unroll
-        for (int a1 = 0; a1 < 5; ++a1)
-          if (bt5(q1r, a1) != 0.0f) sr = fmaf(bt5(q1r, a1), Rw[a1][c], sr);
+        for (int a1 = 1; a1 < 5; ++a1) sr = fmaf(c1v[a1], Rw[a1][c], sr);
         R[c] = sr;
       }
       // columns: level 2 (stride 3), then level 1
@@ -202,11 +214,9 @@ __global__ __launch_bounds__(320) void input_xform5(const float* __restrict__ x,
         }
         float o[5];
         bt5_vec(v5, o);
+        float* __restrict__ vq = vm + (size_t)(((q2r * 5 + q2c) * 5 + q1r) * 5) * pstride;
 #pragma unroll
-        for (int q1c = 0; q1c < 5; ++q1c) {
-          const int p = ((q2r * 5 + q2c) * 5 + q1r) * 5 + q1c;
-          vp[(size_t)p * pstride] = o[q1c];
-        }
+        for (int q1c = 0; q1c < 5; ++q1c) (vq + (size_t)q1c * pstride)[t] = o[q1c];
       }
     }
   }
@@ -876,7 +886,8 @@ hipError_t launch_kernel_xform5(const nwg_plan_info& g, const float* w, float* U
   return hipGetLastError();
 }
 
-hipError_t launch_input_xform5(const nwg_plan_info& g, const float* x, float* V, hipStream_t s) {
+hipError_t launch_input_xform5(const nwg_plan_info& g, const float* x, float* V, hipStream_t s,
+                               int ld) {
   if (g.n != 1 && g.n != 2) return hipErrorInvalidValue;
   const int Mn = g.n == 1 ? 3 : 9, Ln = g.n == 1 ? 5 : 17;
   // up to 64 tiles per box
@@ -888,13 +899,16 @@ hipError_t launch_input_xform5(const nwg_plan_info& g, const float* x, float* V,
   if (blocks > 0x7fffffffLL || g.M > 65535) return hipErrorInvalidValue;
   const size_t lds = (size_t)((RY - 1) * Mn + Ln) * ((RX - 1) * Mn + Ln) * sizeof(float);
   dim3 grid((unsigned)blocks, (unsigned)g.M);
-  const int T = (int)g.T;
+  if (ld == 0) ld = (int)g.T;
+  // e / BW as the high word of e * magic: exact for e BW < 2^32 (BW > 1)
+  const unsigned BW = (unsigned)((RX - 1) * Mn + Ln);
+  const unsigned magic = (unsigned)((0x100000000ULL + BW - 1) / BW);
   if (g.n == 1)
     hipLaunchKernelGGL(input_xform5<1>, grid, dim3(64), lds, s, x, V, g.M, g.H, g.W, g.pad, g.th,
-                       g.tw, T, RX, RY, nbx, nby);
+                       g.tw, ld, RX, RY, nbx, nby, magic);
   else
     hipLaunchKernelGGL(input_xform5<2>, grid, dim3(320), lds, s, x, V, g.M, g.H, g.W, g.pad,
-                       g.th, g.tw, T, RX, RY, nbx, nby);
+                       g.th, g.tw, ld, RX, RY, nbx, nby, magic);
   return hipGetLastError();
 }
 

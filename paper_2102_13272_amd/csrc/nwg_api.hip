@@ -256,6 +256,7 @@ int run_pipelined(nwg_plan* p, const float* x, hipStream_t s) {
 // The kernel transform into a plan's own U (plans on the level-1 taps hold
 // those; the stage call writes the layouts of nwg.h).
 hipError_t own_kxform(const nwg_plan_info& g, const float* w, float* U, hipStream_t s) {
+  if (nwg::taps5_applies(g)) return nwg::launch_kernel_xform_taps5(g, w, U, s);
   return nwg::taps_applies(g) ? nwg::launch_kernel_xform_taps(g, w, U, s)
                               : launch_kxform(g, w, U, s);
 }
@@ -322,6 +323,17 @@ int run_steps(nwg_plan* p, const nwg_plan_info& g, const Workspace& ws, const fl
   } else if (g.pipeline_parts > 1) {
     if (!p) return fail(NWG_EUNSUPPORTED, "the two-stream pipeline needs a plan");
     rc = run_pipelined(p, x, s);
+  } else if (nwg::taps5_applies(g)) {
+    float* Z = nwg::taps5_z(g, ws.V);
+    rc = timed(p, 1, s, "input transform launch", [&] {
+      return nwg::launch_input_xform5(g, x, ws.V, s, (int)((g.T + 3) & ~3LL));
+    });
+    if (rc != NWG_OK) return rc;
+    rc = timed(p, 2, s, "contraction launch",
+               [&] { return nwg::launch_contract_taps5(g, U, ws.V, Z, s); });
+    if (rc != NWG_OK) return rc;
+    return timed(p, 3, s, "output transform launch",
+                 [&] { return nwg::launch_output_xform5(g, Z, y, s, 1, true); });
   } else if (nwg::taps_applies(g)) {
     rc = timed(p, 1, s, "input transform launch", [&] {
       return nwg::launch_input_xform_taps(g, x, ws.V, mix_scratch_of(g, ws.Yh), s);
@@ -380,10 +392,14 @@ nwg_plan* create_plan(const nwg_plan_info& g, int tile) {
   };
   const size_t vb = nwg::plan_holds_v(g) ? g.v_bytes : 0;
   const size_t zb = nwg::plan_holds_z(g) ? nwg::zalloc_bytes(g) : 0;
-  if (!alloc(&p->U, g.u_bytes, "U") || !alloc(&p->V, vb, "V") || !alloc(&p->Yh, zb, "Yhat")) {
+  // V and Z in one block (the level-1 taps of F(3,3) divide it in another place)
+  const size_t vz = (vb + 255) & ~(size_t)255;
+  if (!alloc(&p->U, g.u_bytes, "U") || !alloc(&p->V, vb ? vz + zb : 0, "V and Yhat") ||
+      !alloc(&p->Yh, vb ? 0 : zb, "Yhat")) {
     nwg_plan_destroy(p);    // frees nothing it did not allocate; keeps the message
     return nullptr;
   }
+  if (vb && zb) p->Yh = p->V + vz / sizeof(float);
   return p;
 }
 
@@ -431,7 +447,7 @@ void nwg_plan_destroy(nwg_plan* p) {
   if (!p) return;
   if (p->U) hipFree(p->U);
   if (p->V) hipFree(p->V);
-  if (p->Yh) hipFree(p->Yh);
+  if (p->Yh && !p->V) hipFree(p->Yh);                  // else within V's block
   for (auto& r : p->pending) {
     hipEventDestroy(r.start);
     hipEventDestroy(r.stop);

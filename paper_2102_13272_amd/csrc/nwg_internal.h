@@ -398,7 +398,9 @@ hipError_t launch_input_contract(const nwg_plan_info& g, const float* x, const f
                                  hipStream_t s);
 // the F(3,3) tile (depth 1-2): U [P][M][N], V [P][M][T], Z [P/25][9][N][T]
 hipError_t launch_kernel_xform5(const nwg_plan_info& g, const float* w, float* U, hipStream_t s);
-hipError_t launch_input_xform5(const nwg_plan_info& g, const float* x, float* V, hipStream_t s);
+// ld: V's values per row, T if 0
+hipError_t launch_input_xform5(const nwg_plan_info& g, const float* x, float* V, hipStream_t s,
+                               int ld = 0);
 hipError_t launch_contract5(const nwg_plan_info& g, const float* U, const float* V, float* Z,
                             hipStream_t s);
 // parts > 1 / fold9: the fused kernel's partial Z9 buffers (see f33.hip)

@@ -590,6 +590,22 @@ bool taps_applies(const nwg_plan_info& g) {
   return rows * gm.np * 9.0 * g.M * (Np > Tp ? Np : Tp) * 4.0 < 2147483648.0;
 }
 
+bool taps5_applies(const nwg_plan_info& g) {
+  if (g.tile != NWG_TILE_F3X3_3X3 || g.n != 2 || g.depthwise) return false;
+  if (g.fused_input || g.fused_output || g.M % 4) return false;
+  const double Np = 4.0 * ((g.N + 3) / 4), Tp = 4.0 * ((g.T + 3) / 4);
+  if (900.0 * g.M * Np > (double)g.u_bytes) return false;
+  if (2500.0 * g.M * Tp + 900.0 * g.N * (double)g.T > (double)g.v_bytes + (double)g.yhat_bytes)
+    return false;
+  // a block's chain over many channels, with few blocks, is longer than that of the
+  // 5 row digits apart (256 -> 16 channels, 16 tiles: 64.5 us against 59.8; 128 ->
+  // 128: 45.3 against 46.0)
+  if (g.M > 128 && 25.0 * ((g.N + 31) / 32) * (double)((g.T + 31) / 32) <= 128.0) return false;
+  // a group's byte offsets in 31 bits (the dropped stores' on top of them)
+  return 100.0 * g.M * (Np > Tp ? Np : Tp) < 2147483648.0 &&
+         36.0 * g.N * (double)g.T < 1073741824.0;
+}
+
 // ---- direct kernels ----------------------------------------------------------
 
 int direct_toeplitz_row(int r, int wc) {
@@ -653,8 +669,14 @@ bool direct_fits(const nwg_plan_info& g, const DirectShape& d) {
 // Plans on the level-1 taps: 9 of 16 points of V and 4 values of U, some 5 TB/s
 // (the mixed nest at depth 4 waits more for its chain over the channels), and
 // 160 TFLOP/s where the contraction adds to that;
-// fitted to 2300 layers (8 in 10 within 15 %).
+// fitted to 2300 layers (8 in 10 within 15 %).  F(3,3) likewise, fitted to 86.
 double nest_us(const nwg_plan_info& g) {
+  if (taps5_applies(g)) {
+    const double MN = (double)g.M * g.N, T = (double)g.T;
+    const double mb = 1e-6 * (900.0 * MN + 5000.0 * g.M * T + 1800.0 * g.N * T +
+                              4.0 * g.B * ((double)g.M * g.H * g.W + (double)g.N * g.Ho * g.Wo));
+    return 25.0 + 0.09 * g.M + 0.23 * mb + 0.0064 * 1250e-6 * MN * T;
+  }
   if (taps_applies(g)) {
     const GroupMap gm = taps_groups(g);
     const double L = (double)gm.np * gm.np, MN = (double)g.M * g.N, MT = (double)g.M * g.T;

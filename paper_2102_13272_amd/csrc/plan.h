@@ -86,6 +86,10 @@ GroupMap group_map(const nwg_plan_info& g);
 bool taps_applies(const nwg_plan_info& g);
 // The list of groups those plans compute (group_map, or every group).
 GroupMap taps_groups(const nwg_plan_info& g);
+// Dense F(3,3) plans at depth 2 whose nwg_conv2d runs on the level-1 taps
+// (taps5.hip): whole chunks of 4 channels, and V with rows of whole quads and the
+// smaller Z behind it within the memory of the plan's V and Z, which lie together.
+bool taps5_applies(const nwg_plan_info& g);
 
 // Launch shape of a direct kernel (direct.hip), kDirectNone where the nest is
 // the faster one.

@@ -301,24 +301,6 @@ __global__ __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(2)
   wait_vmcnt<0>();                                     // the repeated tail loads land before exit
 }
 
-// Work-groups of the kernel that fit on one CU of device dev, asked once per
-// (device, kernel); 0 if the query fails.
-int taps_occupancy(int dev, const void* kernel, int threads) {
-  static std::mutex mu;
-  static std::map<std::pair<int, const void*>, int> cache;
-  std::lock_guard<std::mutex> lock(mu);
-  const auto key = std::make_pair(dev, kernel);
-  const auto it = cache.find(key);
-  if (it != cache.end()) return it->second;
-  int b = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, kernel, threads, 0) != hipSuccess) {
-    (void)hipGetLastError();
-    b = 0;
-  }
-  cache[key] = b;
-  return b;
-}
-
 template <int BM, int BN, int WM, int WN>
 hipError_t launch(const nwg_plan_info& g, const float* U, const float* V, float* Z, hipStream_t s) {
   const int T = (int)g.T, Np = (g.N + 3) & ~3, Tp = (T + 3) & ~3;
@@ -340,6 +322,22 @@ hipError_t launch(const nwg_plan_info& g, const float* U, const float* V, float*
 }
 
 }  // namespace
+
+int taps_occupancy(int dev, const void* kernel, int threads) {
+  static std::mutex mu;
+  static std::map<std::pair<int, const void*>, int> cache;
+  std::lock_guard<std::mutex> lock(mu);
+  const auto key = std::make_pair(dev, kernel);
+  const auto it = cache.find(key);
+  if (it != cache.end()) return it->second;
+  int b = 0;
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, kernel, threads, 0) != hipSuccess) {
+    (void)hipGetLastError();
+    b = 0;
+  }
+  cache[key] = b;
+  return b;
+}
 
 hipError_t launch_contract_taps(const nwg_plan_info& g, const float* U, const float* V, float* Z,
                                 hipStream_t s) {

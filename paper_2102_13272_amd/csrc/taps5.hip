@@ -1,0 +1,348 @@
+// The channel contraction of F(3,3) chains at depth 2 from level-1 taps.
+//
+// Of a group (level-2 digits) U keeps the 3 x 3 level-1 taps instead of the 25
+// points, [25][3 k1r + k1c][M][Np], and this kernel forms the points in registers
+// with G (40 additions per 25 MFMA operands).  V holds the points, [25][5 q1r +
+// q1c][M][Tp] (Np, Tp: N, T rounded up to 4), and Z comes out with level 1 done on
+// both axes, [25][3 i1r + i1c][N][T]: 9 values of 25 instead of 15.
+//
+// Work-group: a BM x BN block of (n, t) of one group, all 25 points at once (25
+// accumulators of 16 x 16 per wavefront), so that a group's fold is in registers
+// and a barrier comes every 25 products.  A chunk is 4 channels of U's 9 planes and
+// V's 25; four LDS stages filled by direct global->LDS loads, two to three chunks
+// in flight, running on across the work-group's items (persistent; blocks of one
+// V column are neighbours on an XCD).  A chunk's fragments are read one chunk
+// ahead, while the matrix units work on the one before.
+//
+// Bound by the matrix units (half busy), by the copies to LDS (without them 174 us
+// of 227) and by the 3 other vector instructions per product.  128 -> 128 channels,
+// r = 9, 784 tiles (16 GFLOP, 251 MB of V): 217 us against 213 of the contraction
+// of points it replaces, which leaves Z for the output transform at 15 values a
+// group (59 us against 44), and U at 25 (kernel transform 35 us against 20).  Few
+// channels gain more, since a block is 32 or 64 by 32, not 64 by 64: 8 -> 16
+// channels, 392 tiles 52.6 us a call -> 36; 132 layers of 1 to 6720 tiles 0.85 of
+// the time in the geometric mean.  32 (t) per wavefront spilled (340 us).
+#include <cstdint>
+
+#include "nwg_internal.h"
+#include "taps.h"
+#include "taps_device.h"
+
+namespace nwg {
+namespace {
+
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+
+constexpr int kCh = 4;                       // channels of a chunk
+
+// Place of column c in row k (channel) of a staged plane of COLS columns: the 4
+// channels of a fragment lie in different banks.
+template <int COLS>
+__device__ __forceinline__ int place(int k, int c) {
+  return COLS >= 64 ? (c + 16 * (k & 3)) & (COLS - 1)
+         : COLS == 32 ? (c + 16 * ((k >> 1) & 1)) & 31 : c;
+}
+
+// A resource over the bytes of a group
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t read_rsrc(const float* p, unsigned bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p), 0, (int)bytes, 0x00020000);
+}
+
+// G of F(3,3) on one axis
+__device__ __forceinline__ void g5_vec(float w0, float w1, float w2, float (&u)[5]) {
+  const float s = w0 + w2;
+  u[0] = w0;
+  u[1] = s + w1;
+  u[2] = s - w1;
+  u[3] = fmaf(4.0f, w2, fmaf(2.0f, w1, w0));
+  u[4] = w2;
+}
+
+template <int BM, int BN, int WM, int WN>
+__global__ __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(2))) void contract_taps5(
+    const float* __restrict__ U, const float* __restrict__ V, float* __restrict__ Z, int M, int N,
+    int T, int Np, int Tp, int ntb, int nnb, int wpx) {
+  static_assert(BM == 16 * WM && BN == 16 * WN, "16 x 16 per wavefront");
+  constexpr int NW = WM * WN;
+  // quads of a chunk: A's in whole loads, then B's
+  constexpr int QA = (9 * BM + 63) / 64 * 64, QB = 25 * BN;
+  constexpr int LOADS = (QA + QB + 63) / 64;           // of the work-group
+  constexpr int LPW = (LOADS + NW - 1) / NW;           // per wavefront (the last ones to spare)
+  constexpr int STAGE = LPW * NW * 256;
+  __shared__ float S0[STAGE], S1[STAGE], S2[STAGE], S3[STAGE];
+
+  // this work-group's items: first + i * wpx, i < mine
+  const unsigned items = (unsigned)ntb * (unsigned)nnb * 25u;
+  const unsigned xcd = blockIdx.x % 8, jx = blockIdx.x / 8;
+  const unsigned q = items / 8, rem = items % 8;
+  const unsigned xstart = xcd < rem ? xcd * (q + 1) : rem * (q + 1) + (xcd - rem) * q;
+  const unsigned xcount = q + (xcd < rem ? 1 : 0);
+  const int mine = xcount > jx ? (int)((xcount - 1 - jx) / (unsigned)wpx + 1) : 0;
+  if (mine == 0) return;                               // uniform over the work-group
+  const unsigned first = xstart + jx;
+
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wm = wave / WN, wn = wave % WN;
+  const int lr = lane & 15, lk = lane >> 4;
+  const int nk = M / kCh;
+
+  floatx4 acc[25];
+#pragma unroll
+  for (int p = 0; p < 25; ++p) acc[p] = floatx4{0.f, 0.f, 0.f, 0.f};
+  const int pa = lk * BM + place<BM>(lk, wm * 16 + lr);
+  const int pb = 4 * QA + lk * BN + place<BN>(lk, wn * 16 + lr);
+
+  // request cursor: item ri, chunk rc.  Load j of this wavefront copies quads
+  // (wave + j NW) * 64 + lane of the chunk's buffer (A's planes, then B's).
+  unsigned off[LPW];                                   // bytes
+  const unsigned ub = 36u * (unsigned)M * (unsigned)Np, vb = 100u * (unsigned)M * (unsigned)Tp;
+  __amdgpu_buffer_rsrc_t ur, vr;
+  int ri = 0, rc = 0;
+  auto split = [&](int i, int& g, int& tb, int& nb) {
+    unsigned b = first + (unsigned)(i * wpx);
+    nb = (int)(b % (unsigned)nnb);
+    b /= (unsigned)nnb;
+    tb = (int)(b % (unsigned)ntb);
+    g = (int)(b / (unsigned)ntb);
+  };
+  auto set_req_item = [&](int i) {
+    int g, tb, nb;
+    split(i, g, tb, nb);
+    ur = read_rsrc(U + (size_t)g * 9 * M * Np, ub);
+    vr = read_rsrc(V + (size_t)g * 25 * M * Tp, vb);
+#pragma unroll
+    for (int j = 0; j < LPW; ++j) {
+      const int f = (wave + j * NW) * 64 + lane;
+      const bool a = f < QA;
+      const int fb = f - QA;
+      const int row = a ? f / (BM / 4) : fb / (BN / 4);
+      const int at = a ? f % (BM / 4) : fb % (BN / 4);
+      const int plane = row / kCh, k = row % kCh;
+      // the column quad whose place this is
+      const int turn = 4 * k, half = 4 * ((k >> 1) & 1);
+      const int qa = BM >= 64 ? at - turn : BM == 32 ? at - half : at;
+      const int qb = BN >= 64 ? at - turn : BN == 32 ? at - half : at;
+      const int ld = a ? Np : Tp;
+      // (quads past the row re-read its last)
+      int c = a ? nb * BM + 4 * (qa & (BM / 4 - 1)) : tb * BN + 4 * (qb & (BN / 4 - 1));
+      if (c > ld - 4) c = ld - 4;
+      off[j] = plane < (a ? 9 : 25) ? (unsigned)((plane * M + k) * ld + c) * 4u : 0u;
+    }
+  };
+  // past the last item the last chunk is requested again, into a buffer that
+  // is never read, so every step issues the same loads
+  auto request = [&](float* S) {
+    const int su = rc * kCh * Np * 4, sv = rc * kCh * Tp * 4;
+#pragma unroll
+    for (int j = 0; j < LPW; ++j) {
+      const bool a = wave + j * NW < QA / 64;          // uniform
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(
+          a ? ur : vr, (__attribute__((address_space(3))) void*)(S + (wave + j * NW) * 256), 16,
+          (int)off[j], a ? su : sv, 0, 0);
+    }
+  };
+  auto advance = [&]() {
+    if (rc + 1 < nk) {
+      ++rc;
+    } else if (ri + 1 < mine) {
+      ++ri;
+      rc = 0;
+      set_req_item(ri);
+    }
+  };
+  // item i done: the level-1 fold on both axes, and Z
+  auto finish = [&](int i) {
+    int g, tb, nb;
+    split(i, g, tb, nb);
+    floatx4 z[3][3];
+#pragma unroll
+    for (int i1c = 0; i1c < 3; ++i1c) {
+      floatx4 h[5];
+#pragma unroll
+      for (int qr = 0; qr < 5; ++qr) {
+        const floatx4* a = acc + 5 * qr;
+        h[qr] = i1c == 0   ? a[0] + a[1] + a[2] + a[3]
+                : i1c == 1 ? a[1] - a[2] + 2.0f * a[3]
+                           : a[1] + a[2] + 4.0f * a[3] + a[4];
+      }
+      z[0][i1c] = h[0] + h[1] + h[2] + h[3];
+      z[1][i1c] = h[1] - h[2] + 2.0f * h[3];
+      z[2][i1c] = h[1] + h[2] + 4.0f * h[3] + h[4];
+    }
+#pragma unroll
+    for (int p = 0; p < 25; ++p) acc[p] = floatx4{0.f, 0.f, 0.f, 0.f};
+    const size_t plane = (size_t)N * T;
+    const auto rs = span_rsrc(reinterpret_cast<float4*>(Z + (size_t)g * 9 * plane),
+                              (unsigned)(36 * plane));
+    const int col = tb * BN + wn * 16 + lr;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int row = nb * BM + wm * 16 + 4 * lk + v;
+      const unsigned at = row < N && col < T ? (unsigned)(row * T + col) * 4u : kDrop;
+#pragma unroll
+      for (int o = 0; o < 9; ++o) drop_store1(rs, at, z[o / 3][o % 3][v], o * (unsigned)plane * 4u);
+    }
+  };
+  struct Frag {
+    float a[9], b[25];
+  };
+  auto read = [&](Frag& f, const float* S) {
+#pragma unroll
+    for (int t = 0; t < 9; ++t) f.a[t] = S[t * kCh * BM + pa];
+#pragma unroll
+    for (int p = 0; p < 25; ++p) f.b[p] = S[p * kCh * BN + pb];
+  };
+  auto multiply = [&](const Frag& f) {
+    float xr[3][5];                                    // G along the rows, per tap column
+#pragma unroll
+    for (int c = 0; c < 3; ++c) g5_vec(f.a[c], f.a[3 + c], f.a[6 + c], xr[c]);
+#pragma unroll
+    for (int qr = 0; qr < 5; ++qr) {
+      float u[5];
+      g5_vec(xr[0][qr], xr[1][qr], xr[2][qr], u);
+#pragma unroll
+      for (int qc = 0; qc < 5; ++qc)
+        acc[5 * qr + qc] =
+            __builtin_amdgcn_mfma_f32_16x16x4f32(u[qc], f.b[5 * qr + qc], acc[5 * qr + qc], 0, 0, 0);
+    }
+  };
+  int it = 0, kc = 0;                                  // item and chunk being multiplied
+  Frag f0, f1;
+  // Chunk c's fragments in fc, chunk c + 1 in S1 and in flight: wait for it, read
+  // its fragments, and multiply chunk c meanwhile.  The new request (c + 3)
+  // overwrites chunk c - 1, whose fragments every wavefront had multiplied before
+  // this barrier.
+  auto step = [&](const Frag& fc, Frag& fn, const float* Sn, float* Sr) {
+    wait_vmcnt<LPW>();
+    __builtin_amdgcn_s_barrier();
+    read(fn, Sn);
+    request(Sr);
+    multiply(fc);
+    // the reads among the first products, the requests among the rest (the compiler
+    // puts the requests first, and they keep the matrix units waiting: 253 against
+    // 227 us, with the reads sunk to where they are used 246)
+#pragma unroll
+    for (int k = 0; k < 9; ++k) {
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+      __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+    }
+#pragma unroll
+    for (int k = 0; k < LPW; ++k) {
+      __builtin_amdgcn_sched_group_barrier(0x008, 25 / LPW / 2, 0);
+      __builtin_amdgcn_sched_group_barrier(0x010, 1, 0);
+    }
+    advance();
+    if (++kc == nk) {
+      finish(it);
+      ++it;
+      kc = 0;
+    }
+  };
+
+  set_req_item(0);
+  request(S0);
+  advance();
+  request(S1);
+  advance();
+  request(S2);
+  advance();
+  wait_vmcnt<2 * LPW>();
+  __builtin_amdgcn_s_barrier();
+  read(f0, S0);
+  // (left at once after the last chunk: a step that may be skipped would leave the
+  // compiler a path on which the next one's reads follow their request directly,
+  // and it would wait there for every load in flight)
+  for (;;) {
+    step(f0, f1, S1, S3);
+    if (it >= mine) break;
+    step(f1, f0, S2, S0);
+    if (it >= mine) break;
+    step(f0, f1, S3, S1);
+    if (it >= mine) break;
+    step(f1, f0, S0, S2);
+    if (it >= mine) break;
+  }
+  wait_vmcnt<0>();                                     // the repeated tail loads land before exit
+}
+
+template <int BM, int BN, int WM, int WN>
+hipError_t launch(const nwg_plan_info& g, const float* U, const float* V, float* Z, hipStream_t s) {
+  const int T = (int)g.T, Np = (g.N + 3) & ~3, Tp = (T + 3) & ~3;
+  const int ntb = (T + BN - 1) / BN, nnb = (g.N + BM - 1) / BM;
+  if ((double)ntb * nnb * 25.0 >= 2147483648.0) return hipErrorInvalidValue;
+  int dev = 0, cus = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+  if (e != hipSuccess) return e;
+  const auto k = &contract_taps5<BM, BN, WM, WN>;
+  const int occ = taps_occupancy(dev, reinterpret_cast<const void*>(k), 64 * WM * WN);
+  if (occ <= 0 || cus < 8) return hipErrorInvalidValue;
+  const int wpx = cus / 8 * occ;                       // work-groups per XCD
+  k<<<8 * wpx, 64 * WM * WN, 0, s>>>(U, V, Z, g.M, g.N, T, Np, Tp, ntb, nnb, wpx);
+  return hipGetLastError();
+}
+
+// w -> U: one thread per (output channel n, input channel m), G of level 2 only
+__global__ __launch_bounds__(256) void kernel_xform_taps5(const float* __restrict__ w,
+                                                          float* __restrict__ U, int M, int N,
+                                                          int r, long long nthreads) {
+  const long long id = (long long)blockIdx.x * 256 + threadIdx.x;
+  if (id >= nthreads) return;
+  const int n = (int)(id % N), m = (int)(id / N);
+  const int Np = (N + 3) & ~3;
+  const float* __restrict__ wp = w + ((size_t)n * M + m) * r * r;
+  float wk[9][9];                                      // tap k1 + 3 k2
+#pragma unroll
+  for (int i = 0; i < 9; ++i)
+#pragma unroll
+    for (int j = 0; j < 9; ++j) wk[i][j] = (i < r && j < r) ? wp[i * r + j] : 0.0f;
+  float* __restrict__ up = U + (size_t)m * Np + n;
+  const size_t plane = (size_t)M * Np;
+#pragma unroll
+  for (int k1r = 0; k1r < 3; ++k1r) {
+    float xr[9][5];                                    // G along the rows, per column
+#pragma unroll
+    for (int j = 0; j < 9; ++j) g5_vec(wk[k1r][j], wk[3 + k1r][j], wk[6 + k1r][j], xr[j]);
+#pragma unroll
+    for (int q2r = 0; q2r < 5; ++q2r)
+#pragma unroll
+      for (int k1c = 0; k1c < 3; ++k1c) {
+        float u[5];
+        g5_vec(xr[k1c][q2r], xr[3 + k1c][q2r], xr[6 + k1c][q2r], u);
+#pragma unroll
+        for (int q2c = 0; q2c < 5; ++q2c)
+          up[(size_t)((5 * q2r + q2c) * 9 + 3 * k1r + k1c) * plane] = u[q2c];
+      }
+  }
+}
+
+}  // namespace
+
+float* taps5_z(const nwg_plan_info& g, float* V) {
+  return V + (size_t)625 * g.M * ((g.T + 3) & ~3LL);
+}
+
+hipError_t launch_kernel_xform_taps5(const nwg_plan_info& g, const float* w, float* U,
+                                     hipStream_t s) {
+  if (!taps5_applies(g)) return hipErrorInvalidValue;
+  const long long nthreads = (long long)g.N * g.M;
+  kernel_xform_taps5<<<(unsigned)((nthreads + 255) / 256), 256, 0, s>>>(w, U, g.M, g.N, g.r,
+                                                                        nthreads);
+  return hipGetLastError();
+}
+
+hipError_t launch_contract_taps5(const nwg_plan_info& g, const float* U, const float* V, float* Z,
+                                 hipStream_t s) {
+  if (!taps5_applies(g) || (((uintptr_t)U | (uintptr_t)V) & 15)) return hipErrorInvalidValue;
+  auto area = [&](int bm, int bn) {
+    return (double)((g.N + bm - 1) / bm * bm) * (double)((g.T + bn - 1) / bn * bn);
+  };
+  // with no more than a block a CU, the time of one
+  const bool few = (g.N + 63) / 64 * ((g.T + 31) / 32) * 25 <= 256;
+  if (!few && area(64, 32) <= 1.1 * area(32, 32)) return launch<64, 32, 4, 2>(g, U, V, Z, s);
+  return launch<32, 32, 2, 2>(g, U, V, Z, s);
+}
+
+}  // namespace nwg

@@ -125,3 +125,50 @@ def test_f23_layers_on_taps_match_oracle(case):
         torch.cuda.synchronize()
         assert_close(y.cpu().numpy(), z.cpu().numpy().astype(np.float64), rel_tol=1e-5,
                      what=f"{case} against the stage calls")
+
+
+F33 = nwg.NWG_TILE_F3X3_3X3
+
+# F(3,3) chains of depth 2: (B, M, N, H, W, r, pad)
+F33_CASES = [
+    (1, 4, 64, 9, 9, 4, 1),           # one tile, one chunk
+    (1, 8, 3, 18, 40, 5, 2),          # T = 10, few channels
+    (2, 20, 33, 30, 25, 6, 2),        # N one past a block, T = 24
+    (1, 12, 66, 60, 57, 7, 3),        # N two past a block, T = 49: rows of 52
+    (3, 36, 70, 56, 50, 8, 3),        # T = 126
+    (4, 32, 128, 56, 56, 9, 4),       # T = 196
+    (2, 64, 40, 100, 91, 9, 0),       # T = 220
+    (1, 16, 16, 256, 130, 5, 2),      # two boxes across
+    (1, 6, 20, 30, 30, 5, 2),         # M = 6: the contraction of points
+]
+
+
+@pytest.mark.parametrize("case", F33_CASES, ids=lambda c: "B%d_M%d_N%d_%dx%d_r%d_p%d" % c)
+def test_f33_layers_on_taps_match_oracle(case):
+    B, M, N, H, W, r, pad = case
+    print(f"F(3,3) taps case {case}", flush=True)
+    _, x, w = make_case(B, M, N, H, W, r, pad, seed=sum(case), x_dist="normal",
+                        w_dist="fanin_normal")
+    xd, wd = dev(x), dev(w)
+    ref = direct_conv2d(x, w, pad)
+    with nwg.Plan(B, M, N, H, W, r, pad, tile=F33) as plan:
+        y = torch.full(plan.y_shape, float("nan"), device="cuda")
+        for _ in range(2):
+            plan.conv2d(xd, wd, y)
+        torch.cuda.synchronize()
+        # F(3,3) at depth 2: some 3e-6 of the output
+        assert_close(y.cpu().numpy(), ref, rel_tol=2e-5, what=str(case))
+        z = torch.full(plan.y_shape, float("nan"), device="cuda")
+        nwg.conv2d_noalloc(xd, wd, z, pad, tile=F33)
+        torch.cuda.synchronize()
+        assert torch.equal(y, z)
+        U = torch.empty(plan.u_shape, device="cuda")
+        V = torch.empty(plan.v_shape, device="cuda")
+        Z = torch.empty(plan.z_shape, device="cuda")
+        plan.kernel_transform(wd, U)
+        plan.input_transform(xd, V)
+        plan.contract(U, V, Z)
+        plan.output_transform(Z, z)
+        torch.cuda.synchronize()
+        assert_close(y.cpu().numpy(), z.cpu().numpy().astype(np.float64), rel_tol=2e-5,
+                     what=f"{case} against the stage calls")
