@@ -846,60 +846,67 @@ __global__ __launch_bounds__(64) void output_xform_mix23(const float4* __restric
       }
 }
 
-// Depth 3 (NO = 1): levels 2 and 3 straight to y, one thread per (tile t,
-// output block (i3r, i3c), channel n), lanes on consecutive tiles: over the
-// level-3 branches whose A^T coefficient for its block is nonzero (a
-// work-group-uniform test), level2_reduce gives the branch's 4 x 4 block and
-// the thread accumulates its own 4 x 4 output block.  Nine times the threads
-// of a (tile, channel) split (the 144 accumulators of output_xform_mix23 leave
-// one wavefront per CU on layers of a few hundred tiles).  A block's
-// branches overlap its neighbours' (each Z value is read by up to nine
-// blocks), so the work-groups are numbered per XCD (xcd_remap), tile block
-// fastest, then output block, then channel: the 9 ntb work-groups of a
-// channel run together on one XCD and share its Z through that XCD's L2.
-__global__ __launch_bounds__(64) void output_xform_mix3(const float4* __restrict__ Z,
-                                                        float* __restrict__ y, int N, int Ho,
-                                                        int Wo, int th, int tw, int T,
-                                                        long long gstride, unsigned long long m0,
-                                                        unsigned long long m1) {
-  const int ntb = (T + 63) / 64;
-  const long long lid = xcd_remap(blockIdx.x, gridDim.x);
-  const int tb = (int)(lid % ntb);
-  const int blk = (int)((lid / ntb) % 9);   // 3 i3r + i3c
-  const int n = (int)(lid / (9LL * ntb));
-  const int t = tb * 64 + threadIdx.x;
-  if (t >= T || n >= N) return;
-  const int i3r = blk / 3, i3c = blk - 3 * i3r;
-  float acc[16];
-#pragma unroll
-  for (int e = 0; e < 16; ++e) acc[e] = 0.0f;
-  const float4* zt = Z + (size_t)n * T + t;
-#pragma unroll 1
-  for (int q3 = 0; q3 < 25; ++q3) {
+// Depth 3 (NO = 1): levels 2 and 3 straight to y.  Work-group: 16 tiles of a
+// channel.  First a thread per (level-3 branch, tile) reduces the branch's Z to
+// its 4 x 4 block in LDS, so that every Z value is read once, in 256-byte runs;
+// then a thread per (row of a block, tile, column of 12) applies level 3's A^T,
+// columns and then rows, to its outputs in the three row blocks (stores run
+// along the rows of y).  Work-groups that share lines of Z lie on one XCD.
+// A thread per output block read each Z value 4.8 times on average, from L2 (64
+// channels, 200 tiles, 74 MB of Z: the call 165.9 us, so 152.4).
+constexpr int kOT = 16, kOP = kOT + 1;      // tiles, and a value's tiles in LDS
+__global__ __launch_bounds__(448) void output_xform_mix3(const float4* __restrict__ Z,
+                                                         float* __restrict__ y, int N, int Ho,
+                                                         int Wo, int th, int tw, int T,
+                                                         long long gstride, unsigned long long m0,
+                                                         unsigned long long m1) {
+  __shared__ float blocks[25 * 16 * kOP];   // [branch][4 rr + cc][tile]
+  const int ntb = (T + kOT - 1) / kOT;
+  const int lid = (int)xcd_remap(blockIdx.x, gridDim.x);
+  const int n = lid / ntb;
+  const int t0 = (lid - n * ntb) * kOT;
+  if (threadIdx.x < 25 * kOT) {
+    const int q3 = threadIdx.x / kOT, tl = threadIdx.x % kOT;
     const int q3r = q3 / 5, q3c = q3 - 5 * q3r;
-    const float c = at5(i3r, q3r) * at5(i3c, q3c);
-    if (c == 0.0f) continue;                // uniform over the work-group
+    float po[4][4] = {};
+    // the dead groups' Z is zero and is not read
     const unsigned live = branch_live<1>(m0, m1, 0, 0, q3r, q3c);
-    if (live == 0) continue;
-    float po[4][4];
-    level2_reduce(zt + (size_t)q3 * 16 * gstride, (size_t)gstride, po, live);
+    if (t0 + tl < T && live != 0)
+      level2_reduce(Z + (size_t)q3 * 16 * gstride + (size_t)n * T + t0 + tl, (size_t)gstride, po,
+                    live);
 #pragma unroll
-    for (int e = 0; e < 16; ++e) acc[e] = fmaf(c, po[e >> 2][e & 3], acc[e]);
+    for (int e = 0; e < 16; ++e) blocks[(q3 * 16 + e) * kOP + tl] = po[e >> 2][e & 3];
   }
+  __syncthreads();
   const int tpi = th * tw;
-  const int b = t / tpi;
-  const int r2 = t - b * tpi;
-  const int ty = r2 / tw, tx = r2 - ty * tw;
-  float* yo = y + ((size_t)b * N + n) * Ho * Wo;
+  for (int task = threadIdx.x; task < 4 * 12 * kOT; task += 448) {
+    const int rr = task / (12 * kOT), rest = task - rr * 12 * kOT;
+    const int tl = rest / 12, c = rest - 12 * tl;
+    const int t = t0 + tl;
+    if (t >= T) continue;
+    const int i3c = c / 4;
+    const float* v = blocks + (4 * rr + c % 4) * kOP + tl;
+    constexpr int BS = 16 * kOP;            // between branches
+    // row i3c of A^T: v0 + v1 + v2 + v3, v1 - v2 + 2 v3, v1 + v2 + 4 v3 + v4
+    const float s2 = i3c == 1 ? -1.0f : 1.0f, s3 = i3c == 0 ? 1.0f : i3c == 1 ? 2.0f : 4.0f;
+    const int ends = i3c == 0 ? 0 : 4 * BS;
+    float h[5];
 #pragma unroll
-  for (int rr = 0; rr < 4; ++rr) {
-    const int row = ty * 12 + 4 * i3r + rr;
-    if (row >= Ho) continue;
-#pragma unroll
-    for (int cc = 0; cc < 4; ++cc) {
-      const int col = tx * 12 + 4 * i3c + cc;
-      if (col < Wo) yo[(size_t)row * Wo + col] = acc[rr * 4 + cc];
+    for (int q3r = 0; q3r < 5; ++q3r) {
+      const float* u = v + 5 * q3r * BS;
+      const float last = u[ends];
+      h[q3r] = fmaf(s3, u[3 * BS], fmaf(s2, u[2 * BS], u[BS])) + (i3c == 1 ? 0.0f : last);
     }
+    const int b = t / tpi;
+    const int r2 = t - b * tpi;
+    const int ty = r2 / tw, tx = r2 - ty * tw;
+    const int row = ty * 12 + rr, col = tx * 12 + c;
+    if (col >= Wo) continue;
+    float* yo = y + (((size_t)b * N + n) * Ho + row) * Wo + col;
+    const float s = h[1] + h[2];
+    if (row < Ho) yo[0] = (h[0] + h[3]) + s;
+    if (row + 4 < Ho) yo[(size_t)4 * Wo] = fmaf(2.0f, h[3], h[1] - h[2]);
+    if (row + 8 < Ho) yo[(size_t)8 * Wo] = fmaf(4.0f, h[3], s) + h[4];
   }
 }
 
@@ -1116,9 +1123,9 @@ hipError_t launch_output_xform_mix(const nwg_plan_info& g, const float* Zf, floa
   const long long gstride = (long long)g.N * g.T;
   const unsigned tb = (unsigned)((g.T + 63) / 64);
   if (no == 1) {
-    const long long nwg = 9LL * tb * g.N;
+    const long long nwg = (g.T + kOT - 1) / kOT * g.N;
     if (nwg > 0x7fffffffLL) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(output_xform_mix3, dim3((unsigned)nwg), dim3(64), 0, s, Z, y, g.N,
+    hipLaunchKernelGGL(output_xform_mix3, dim3((unsigned)nwg), dim3(448), 0, s, Z, y, g.N,
                        g.Ho, g.Wo, g.th, g.tw, (int)g.T, gstride, g.live_prefix[0],
                        g.live_prefix[1]);
     return hipGetLastError();

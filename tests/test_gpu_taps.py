@@ -40,6 +40,9 @@ CASES = [
     (1, 24, 17, 37, 37, 38, 20),      # the last r of depth 4 with digit 3 dead
     (4, 8, 32, 144, 144, 17, 8),      # T = 64: 64-tile input transform
     (3, 8, 129, 108, 72, 19, 9),      # T = 18
+    (3, 8, 2, 60, 11, 9, 4),          # T = 15: the output transform's 16 tiles,
+    (1, 8, 3, 47, 46, 10, 5),         # whole (T = 16),
+    (1, 8, 2, 10, 204, 13, 6),        # and one more (T = 17)
     (1, 12, 20, 30, 30, 13, 6),       # M = 12: the quad layout
     (1, 16, 20, 30, 30, 15, 7),       # r = 15: level-1 digit 3 live, the quad layout
 ]
