@@ -455,14 +455,10 @@ __global__ __launch_bounds__(256) void contract5(const float* __restrict__ U,
 // ---- output transform: one thread per (tile, n) ----------------------------
 // Z [P/25][5][3][N][T] (level-1 columns applied) -> the level-1 rows, then
 // at depth 2 the level-2 A^T on both axes (output row i1r + 3 i2r).
-// FOLD9 (the fused kernel's parts, depth 2): Z9 [P/25][3][3][N][T], level 1
-// already applied on both axes.  parts > 1: the sum of `parts` buffers
-// zpart floats apart.
-template <int NLEV, bool FOLD9 = false>
+template <int NLEV>
 __global__ __launch_bounds__(256) void output_xform5(const float* __restrict__ Z,
                                                      float* __restrict__ y, int N, int Ho,
-                                                     int Wo, int th, int tw, int T, int parts,
-                                                     size_t zpart) {
+                                                     int Wo, int th, int tw, int T) {
   constexpr int Mn = NLEV == 1 ? 3 : 9;
   const int t = blockIdx.x * 256 + threadIdx.x;
   const int n = blockIdx.y;
@@ -488,11 +484,7 @@ __global__ __launch_bounds__(256) void output_xform5(const float* __restrict__ Z
 #pragma unroll
     for (int q = 0; q < 5; ++q)
 #pragma unroll
-      for (int c = 0; c < 3; ++c) {
-        float v = 0.0f;
-        for (int k = 0; k < parts; ++k) v += zp[(size_t)k * zpart + (size_t)(q * 3 + c) * plane];
-        zr[q][c] = v;
-      }
+      for (int c = 0; c < 3; ++c) zr[q][c] = zp[(size_t)(q * 3 + c) * plane];
     level1_rows(zr, out);
   } else {
 #pragma unroll
@@ -509,55 +501,18 @@ __global__ __launch_bounds__(256) void output_xform5(const float* __restrict__ Z
       float zv9[5][3][3];
       size_t pl = plane;
       asm volatile("" : "+s"(pl));
-      if constexpr (FOLD9) {
+      float zr[5][5][3];
 #pragma unroll
-        for (int q2c = 0; q2c < 5; ++q2c)
+      for (int q2c = 0; q2c < 5; ++q2c)
 #pragma unroll
-          for (int i = 0; i < 3; ++i)
+        for (int q = 0; q < 5; ++q)
 #pragma unroll
-            for (int c = 0; c < 3; ++c) {
-              zv9[q2c][i][c] = *zq;
-              zq += pl;
-            }
-        for (int k = 1; k < parts; ++k) {
-          const float* zk = zq - 45 * pl + (size_t)k * zpart;
+          for (int c = 0; c < 3; ++c) {
+            zr[q2c][q][c] = *zq;
+            zq += pl;
+          }
 #pragma unroll
-          for (int q2c = 0; q2c < 5; ++q2c)
-#pragma unroll
-            for (int i = 0; i < 3; ++i)
-#pragma unroll
-              for (int c = 0; c < 3; ++c) {
-                zv9[q2c][i][c] += *zk;
-                zk += pl;
-              }
-        }
-      } else {
-        float zr[5][5][3];
-#pragma unroll
-        for (int q2c = 0; q2c < 5; ++q2c)
-#pragma unroll
-          for (int q = 0; q < 5; ++q)
-#pragma unroll
-            for (int c = 0; c < 3; ++c) {
-              zr[q2c][q][c] = *zq;
-              zq += pl;
-            }
-        // partial sums of a channel-split contraction (parts > 1)
-        for (int k = 1; k < parts; ++k) {
-          const float* zk = zq - 75 * pl + (size_t)k * zpart;
-#pragma unroll
-          for (int q2c = 0; q2c < 5; ++q2c)
-#pragma unroll
-            for (int q = 0; q < 5; ++q)
-#pragma unroll
-              for (int c = 0; c < 3; ++c) {
-                zr[q2c][q][c] += *zk;
-                zk += pl;
-              }
-        }
-#pragma unroll
-        for (int q2c = 0; q2c < 5; ++q2c) level1_rows(zr[q2c], zv9[q2c]);
-      }
+      for (int q2c = 0; q2c < 5; ++q2c) level1_rows(zr[q2c], zv9[q2c]);
       float cr[3];
 #pragma unroll
       for (int i = 0; i < 3; ++i) {
@@ -598,6 +553,66 @@ __global__ __launch_bounds__(256) void output_xform5(const float* __restrict__ Z
       const int col = tx * Mn + k;
       if (col < Wo) yo[(size_t)row * Wo + col] = out[i][k];
     }
+  }
+}
+
+// Depth 2 with level 1 done on both axes: Z9 [25][3 i1r + i1c][N][T] -> y.
+// Work-group: 32 tiles of a channel, whose 225 values go to LDS (128-byte runs,
+// 15 loads a thread in flight); then a thread per (i1r, tile, column of 9)
+// applies level 2's A^T, columns and then rows, and its stores run along the
+// rows of y.  Work-groups that share lines of Z and of y lie on one XCD.
+// 128 channels, 784 tiles (90 MB of Z, 26 MB of y): the call 304.6 us with a
+// thread per tile (81 accumulators, stores 9 values apart), so 286.6.
+constexpr int kZT = 32, kZP = kZT + 1;      // tiles, and a value's tiles in LDS
+__global__ __launch_bounds__(480) void output_xform9(const float* __restrict__ Z,
+                                                     float* __restrict__ y, int N, int Ho,
+                                                     int Wo, int th, int tw, int T) {
+  __shared__ float vals[225 * kZP];         // [group][3 i1r + i1c][tile]
+  const int ntb = (T + kZT - 1) / kZT;
+  const int lid = (int)xcd_remap(blockIdx.x, gridDim.x);
+  const int n = lid / ntb;
+  const int t0 = (lid - n * ntb) * kZT;
+  {
+    const int tl = threadIdx.x % kZT, p0 = threadIdx.x / kZT;       // p0 < 15
+    const int t = t0 + tl < T ? t0 + tl : T - 1;                    // (not stored past T)
+    const size_t plane = (size_t)N * T;
+    const float* zp = Z + (size_t)n * T + t;
+    float v[15];
+#pragma unroll
+    for (int k = 0; k < 15; ++k) v[k] = zp[(size_t)(p0 + 15 * k) * plane];
+#pragma unroll
+    for (int k = 0; k < 15; ++k) vals[(p0 + 15 * k) * kZP + tl] = v[k];
+  }
+  __syncthreads();
+  const int tpi = th * tw;
+  for (int task = threadIdx.x; task < 3 * 9 * kZT; task += 480) {
+    const int i1r = task / (9 * kZT), rest = task - i1r * 9 * kZT;
+    const int tl = rest / 9, c = rest - 9 * tl;
+    const int t = t0 + tl;
+    if (t >= T) continue;
+    const int i2c = c / 3;
+    const float* v = vals + (3 * i1r + c - 3 * i2c) * kZP + tl;
+    constexpr int GS = 9 * kZP;             // between groups
+    // row i2c of A^T: v0 + v1 + v2 + v3, v1 - v2 + 2 v3, v1 + v2 + 4 v3 + v4
+    const float s2 = i2c == 1 ? -1.0f : 1.0f, s3 = i2c == 0 ? 1.0f : i2c == 1 ? 2.0f : 4.0f;
+    const int ends = i2c == 0 ? 0 : 4 * GS;
+    float h[5];
+#pragma unroll
+    for (int q2r = 0; q2r < 5; ++q2r) {
+      const float* u = v + 5 * q2r * GS;
+      const float last = u[ends];
+      h[q2r] = fmaf(s3, u[3 * GS], fmaf(s2, u[2 * GS], u[GS])) + (i2c == 1 ? 0.0f : last);
+    }
+    const int b = t / tpi;
+    const int r2 = t - b * tpi;
+    const int ty = r2 / tw, tx = r2 - ty * tw;
+    const int row = ty * 9 + i1r, col = tx * 9 + c;
+    if (col >= Wo) continue;
+    float* yo = y + (((size_t)b * N + n) * Ho + row) * Wo + col;
+    const float s = h[1] + h[2];
+    if (row < Ho) yo[0] = (h[0] + h[3]) + s;
+    if (row + 3 < Ho) yo[(size_t)3 * Wo] = fmaf(2.0f, h[3], h[1] - h[2]);
+    if (row + 6 < Ho) yo[(size_t)6 * Wo] = fmaf(4.0f, h[3], s) + h[4];
   }
 }
 
@@ -936,23 +951,24 @@ hipError_t launch_contract5(const nwg_plan_info& g, const float* U, const float*
 }
 
 hipError_t launch_output_xform5(const nwg_plan_info& g, const float* Z, float* y, hipStream_t s,
-                                int parts, bool fold9) {
-  if (g.N > 65535 || parts < 1 || (fold9 && g.n != 2)) return hipErrorInvalidValue;
+                                bool fold9) {
+  if (g.N > 65535 || (fold9 && g.n != 2)) return hipErrorInvalidValue;
   const int T = (int)g.T;
-  // parts lie back to back: Z9 parts of P/25 x 9 values per (n, t), else Z
-  const size_t zpart = fold9 ? (size_t)(g.P / 25) * 9 * g.N * g.T : g.yhat_bytes / sizeof(float);
   dim3 grid((unsigned)((T + 255) / 256), (unsigned)g.N);
-  if (g.n == 1)
+  if (g.n == 1) {
     hipLaunchKernelGGL(output_xform5<1>, grid, dim3(256), 0, s, Z, y, g.N, g.Ho, g.Wo, g.th, g.tw,
-                       T, parts, zpart);
-  else if (g.n == 2 && fold9)
-    hipLaunchKernelGGL((output_xform5<2, true>), grid, dim3(256), 0, s, Z, y, g.N, g.Ho, g.Wo,
-                       g.th, g.tw, T, parts, zpart);
-  else if (g.n == 2)
+                       T);
+  } else if (g.n == 2 && fold9) {
+    const long long nwg = (g.T + kZT - 1) / kZT * g.N;
+    if (nwg > 0x7fffffffLL) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(output_xform9, dim3((unsigned)nwg), dim3(480), 0, s, Z, y, g.N, g.Ho, g.Wo,
+                       g.th, g.tw, T);
+  } else if (g.n == 2) {
     hipLaunchKernelGGL(output_xform5<2>, grid, dim3(256), 0, s, Z, y, g.N, g.Ho, g.Wo, g.th, g.tw,
-                       T, parts, zpart);
-  else
+                       T);
+  } else {
     return hipErrorInvalidValue;
+  }
   return hipGetLastError();
 }
 

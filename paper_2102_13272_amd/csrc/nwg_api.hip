@@ -316,7 +316,7 @@ int run_steps(nwg_plan* p, const nwg_plan_info& g, const Workspace& ws, const fl
     });
     if (rc != NWG_OK) return rc;
     return timed(p, 3, s, "output transform launch",
-                 [&] { return nwg::launch_output_xform5(g, ws.Yh, y, s, 1, true); });
+                 [&] { return nwg::launch_output_xform5(g, ws.Yh, y, s, true); });
   } else if (g.fused_input) {
     rc = timed(p, 2, s, "fused input transform + contraction launch",
                [&] { return nwg::launch_input_contract(g, x, U, ws.Yh, s); });
@@ -333,7 +333,7 @@ int run_steps(nwg_plan* p, const nwg_plan_info& g, const Workspace& ws, const fl
                [&] { return nwg::launch_contract_taps5(g, U, ws.V, Z, s); });
     if (rc != NWG_OK) return rc;
     return timed(p, 3, s, "output transform launch",
-                 [&] { return nwg::launch_output_xform5(g, Z, y, s, 1, true); });
+                 [&] { return nwg::launch_output_xform5(g, Z, y, s, true); });
   } else if (nwg::taps_applies(g)) {
     rc = timed(p, 1, s, "input transform launch", [&] {
       return nwg::launch_input_xform_taps(g, x, ws.V, mix_scratch_of(g, ws.Yh), s);

@@ -403,9 +403,9 @@ hipError_t launch_input_xform5(const nwg_plan_info& g, const float* x, float* V,
                                int ld = 0);
 hipError_t launch_contract5(const nwg_plan_info& g, const float* U, const float* V, float* Z,
                             hipStream_t s);
-// parts > 1 / fold9: the fused kernel's partial Z9 buffers (see f33.hip)
+// fold9: Z9, 9 values a group (the fused kernel and taps5.hip; see f33.hip)
 hipError_t launch_output_xform5(const nwg_plan_info& g, const float* Z, float* y, hipStream_t s,
-                                int parts = 1, bool fold9 = false);
+                                bool fold9 = false);
 hipError_t launch_input_contract5(const nwg_plan_info& g, const float* x, const float* U,
                                   float* Zp, hipStream_t s);
 hipError_t launch_contract_output5(const nwg_plan_info& g, const float* V, const float* U,

@@ -142,6 +142,9 @@ F33_CASES = [
     (4, 32, 128, 56, 56, 9, 4),       # T = 196
     (2, 64, 40, 100, 91, 9, 0),       # T = 220
     (1, 16, 16, 256, 130, 5, 2),      # two boxes across
+    (1, 4, 2, 8, 279, 9, 4),          # T = 31: the output transform's 32 tiles,
+    (1, 4, 3, 72, 34, 9, 4),          # whole (T = 32),
+    (1, 4, 2, 25, 95, 9, 4),          # and one more (T = 33)
     (1, 6, 20, 30, 30, 5, 2),         # M = 6: the contraction of points
 ]
 
