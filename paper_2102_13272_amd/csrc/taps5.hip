@@ -18,8 +18,8 @@
 // of 227) and by the 3 other vector instructions per product.  128 -> 128 channels,
 // r = 9, 784 tiles (16 GFLOP, 251 MB of V): 217 us against 213 of the contraction
 // of points it replaces, which leaves Z for the output transform at 15 values a
-// group (59 us against 44), and U at 25 (kernel transform 35 us against 20).  Few
-// channels gain more, since a block is 32 or 64 by 32, not 64 by 64: 8 -> 16
+// group (59 us against 44, both with a thread per tile), and U at 25 (kernel
+// transform 35 us against 20).  Few channels gain more, since a block is 32 or 64 by 32, not 64 by 64: 8 -> 16
 // channels, 392 tiles 52.6 us a call -> 36; 132 layers of 1 to 6720 tiles 0.85 of
 // the time in the geometric mean.  32 (t) per wavefront spilled (340 us).
 #include <cstdint>
